@@ -134,7 +134,8 @@ typedef struct {
  *  bend_scale  multiplies C_b = 3 sqrt(2) kappa/(8 eps^3) of SM eq. (35) (1.0 = as printed)
  *  poisson_rtol, poisson_max_cycles: each Poisson solve of vs_step runs up to max_cycles
  *            refinement cycles until ||b - L_h u||_2 <= rtol ||b||_2 over the three
- *            components (b includes the wall terms); max_cycles in [1, 16].
+ *            components (b includes the wall terms); max_cycles in [1, 16]. In VS_FP64 the
+ *            first cycle solves directly; later cycles are enqueued only after a check missed.
  *  flags     VS_ALLOW_UNSTABLE skips the forward-Euler stability check of vs_step.
  *  rho       fluid density of the inertial variant (SM "Time-dependency and inertial flow",
  *            eq. (36)): (rho/eta) d(omega)/dt - lap omega = -(1/eta) grad phi x grad mu,
@@ -325,8 +326,8 @@ vs_status vs_set_launch_shapes(const vs_grid* grid, const int32_t shapes[7]);
  * table of argument structs (allocated by the batch: a few KB per instance). Grids of a class
  * not tuned yet are tuned first (vs_autotune on the class's first instance; for an FP64
  * class, a grid tuned only by FP32-refined states is tuned again, since its transform form
- * was left at the default). Instances outside the fused forms (FP64 with
- * poisson_max_cycles > 1) are stepped one by one. It creates min(nstreams, groups) HIP
+ * was left at the default). Instances outside the fused forms (grids whose transforms or
+ * column solves need the general kernels) are stepped one by one. It creates min(nstreams, groups) HIP
  * streams (groups: the classes, plus one for those instances; group g runs on stream
  * g % nstreams) and moves every state onto its stream; `stream` (a hipStream_t, NULL =
  * default) is the origin the batch forks from and joins to. vs_batch_step captures two time

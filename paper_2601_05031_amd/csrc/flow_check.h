@@ -16,12 +16,14 @@ __device__ __forceinline__ double fc_wave_sum(double v) {
 }
 
 // Call from every thread of one block (a multiple of 64 threads, at most 1024); sh holds
-// 4 * 16 doubles. last_cycle = 0 (a defect-correction cycle that may be followed by another):
-// the convergence flag gates the next cycle and the miss is not yet an error. log (or null):
-// the step's final check (converged, or the last cycle) appends a record to the per-step log.
+// 4 * 16 doubles. mode: a CheckMode. CK_GATED (a defect-correction cycle that may be followed
+// by another): the convergence flag gates the next cycle and the miss is not yet an error.
+// CK_HALT: a miss only raises IS_HALT, and the correction path the host then runs counts and
+// logs the step. log (or null): the step's final check (converged, or the last cycle) appends a
+// record to the per-step log.
 __device__ inline void flow_check_block(const double* __restrict__ partials, int nblocks,
                                         double rtol, double* scal, int* istat, double* sh,
-                                        int last_cycle = 1, double* log = nullptr) {
+                                        int mode = CK_LAST, double* log = nullptr) {
     double a[4] = {0.0, 0.0, 0.0, 0.0};
     for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
 #pragma unroll
@@ -55,12 +57,22 @@ __device__ inline void flow_check_block(const double* __restrict__ partials, int
             if (rr != rr || bb != bb) r = NAN;
             rel[sidx] = r;
             conv &= (r <= rtol) ? 1 : 0;
+            if (mode == CK_HALT) continue;
             istat[IS_CYCLES] += 1;
             scal[SC_RELRES_LAST] = r;
             if (!isfinite(rr) || !isfinite(bb)) istat[IS_FLAGS] |= ST_NONFINITE;
         }
+        if (mode == CK_HALT) {
+            if (conv) {
+                istat[IS_CYCLES] += 2;
+                istat[IS_PASSED] += 1;
+                scal[SC_RELRES_LAST] = rel[1];
+            } else {
+                istat[IS_HALT] = 1;
+            }
+        }
         istat[IS_CONV] = conv;
-        if (conv || last_cycle) {
+        if (conv || mode == CK_LAST) {
             for (int sidx = 0; sidx < 2; ++sidx) {
                 const double prev = scal[SC_RELRES_MAX];
                 scal[SC_RELRES_MAX] = (rel[sidx] != rel[sidx] || rel[sidx] > prev) ? rel[sidx] : prev;
@@ -79,7 +91,7 @@ __device__ inline void flow_check_block(const double* __restrict__ partials, int
                 istat[IS_LOGN] = n + 1;
             }
         }
-        if (!conv && last_cycle) istat[IS_FLAGS] |= ST_NOCONV;
+        if (!conv && mode == CK_LAST) istat[IS_FLAGS] |= ST_NOCONV;
     }
     __syncthreads();
 }

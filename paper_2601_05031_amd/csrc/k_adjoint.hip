@@ -105,6 +105,8 @@ __global__ __launch_bounds__(kBlock) void k_adj_advect(
         istat[IS_FLAGS] = 0;
         istat[IS_CYCLES] = 0;
         istat[IS_CONV] = 0;
+        istat[IS_HALT] = 0;
+        istat[IS_PASSED] = 0;
     }
     const int nz = d.nz;
     const size_t plane = (size_t)d.ny * nz;

@@ -69,6 +69,8 @@ __device__ __forceinline__ int split_block(int lb, int nb, int& inst) {
     inst = lb / nb;
     return lb - inst * nb;
 }
+// A call's kernels exit at once after a step's direct solve missed rtol (CK_HALT).
+__device__ __forceinline__ bool halted(const int* gate) { return gate && *(const Gl<int>*)gate; }
 template <bool BATCH, class A>
 __device__ __forceinline__ A inst_args(const A& one, const A* __restrict__ tab, int inst) {
     if constexpr (BATCH)
@@ -93,10 +95,11 @@ __global__ __launch_bounds__(kBlock) void k_advance_x(Dims d, SlabGrid sg, AdvAr
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const AdvArgs a = inst_args<BATCH>(one, tab, inst);
+    if (halted(a.gate)) return;
     if (a.ck_part && lb == 0) {
         // the previous step's flow check, off the critical path of this kernel's other blocks
         __shared__ double shc[4 * 16];
-        flow_check_block(a.ck_part, a.ck_nb, a.ck_rtol, a.scal, a.ck_istat, shc, 1, a.ck_log);
+        flow_check_block(a.ck_part, a.ck_nb, a.ck_rtol, a.scal, a.ck_istat, shc, a.ck_mode, a.ck_log);
     }
     const Gl<double>* __restrict__ phi = (const Gl<double>*)a.phi;
     const Gl<T>* __restrict__ mu = (const Gl<T>*)a.mu;
@@ -172,9 +175,10 @@ __global__ __launch_bounds__(kBlock) void k_advance_x2(Dims d, SlabGrid sg, AdvA
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const AdvArgs a = inst_args<BATCH>(one, tab, inst);
+    if (halted(a.gate)) return;
     if (a.ck_part && lb == 0) {
         __shared__ double shc[4 * 16];
-        flow_check_block(a.ck_part, a.ck_nb, a.ck_rtol, a.scal, a.ck_istat, shc, 1, a.ck_log);
+        flow_check_block(a.ck_part, a.ck_nb, a.ck_rtol, a.scal, a.ck_istat, shc, a.ck_mode, a.ck_log);
     }
     const Gl<double>* __restrict__ phi = (const Gl<double>*)a.phi;
     const Gl<T>* __restrict__ mu = (const Gl<T>*)a.mu;
@@ -418,6 +422,7 @@ __global__ __launch_bounds__(kBlock) void k_mu_tile(Dims d, int va_nb, MuArgs on
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nbi, inst);
     const MuArgs va = inst_args<BATCH>(one, tab, inst);
+    if (halted(va.gate)) return;
     const Gl<double>* __restrict__ phi = (const Gl<double>*)va.phi;
     MT* __restrict__ mu = (MT*)va.mu;   // stored through a buffer resource
     const double C_b = va.C_b, eps = va.eps, sigma = va.sigma;
@@ -546,6 +551,7 @@ __global__ __launch_bounds__(kBlock) void k_mu_reg(Dims d, int va_nb, int ni, Mu
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), ngr * nsl, inst);
     const MuArgs va = inst_args<BATCH>(one, tab, inst);
+    if (halted(va.gate)) return;
     const Gl<double>* __restrict__ phi = (const Gl<double>*)va.phi;
     MT* __restrict__ mu = (MT*)va.mu;   // stored through a buffer resource
     const int sl = lb / ngr, gr = lb - sl * ngr;
@@ -685,6 +691,7 @@ __global__ __launch_bounds__(kBlock) void k_va_partials(Dims d, SlabGrid sg, VaA
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const VaArgs va = inst_args<BATCH>(one, tab, inst);
+    if (halted(va.gate)) return;
     const Gl<double>* __restrict__ phi = (const Gl<double>*)va.phi;
     const double eps = va.eps;
     const int bi = lb / sg.gx;
@@ -739,6 +746,7 @@ __global__ __launch_bounds__(kBlock) void k_va_partials2(Dims d, SlabGrid sg, Va
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const VaArgs va = inst_args<BATCH>(one, tab, inst);
+    if (halted(va.gate)) return;
     const Gl<double>* __restrict__ phi = (const Gl<double>*)va.phi;
     const double eps = va.eps;
     const int bi = lb / sg.gx;
@@ -810,6 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_source(Dims d, SrcArgs one, const Sr
     const int inst = BATCH ? ig / d.nx : 0;
     const int i = ig - inst * d.nx;
     const SrcArgs a = inst_args<BATCH>(one, tab, inst);
+    if (halted(a.gate)) return;
     const int t = (lbg - ig * gx) * kBlock + threadIdx.x;
     if (t >= d.ny * d.nz) return;
     const int j = t / d.nz, k = t - (t / d.nz) * d.nz;
@@ -847,6 +856,7 @@ __global__ __launch_bounds__(kBlock) void k_source2(Dims d, SrcArgs one, const S
     const int inst = BATCH ? ig / d.nx : 0;
     const int i = ig - inst * d.nx;
     const SrcArgs a = inst_args<BATCH>(one, tab, inst);
+    if (halted(a.gate)) return;
     const int hz = d.nz >> 1;
     const int t = (lbg - ig * gx) * kBlock + threadIdx.x;
     if (t >= d.ny * hz) return;
@@ -935,6 +945,8 @@ __global__ void k_reset_stats(double* scal, int* istat) {
         istat[IS_FLAGS] = 0;
         istat[IS_CYCLES] = 0;
         istat[IS_CONV] = 0;
+        istat[IS_HALT] = 0;
+        istat[IS_PASSED] = 0;
     }
 }
 

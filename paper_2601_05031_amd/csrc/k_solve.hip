@@ -161,7 +161,8 @@ __global__ __launch_bounds__(64) void k_tridiag_y(Dims d, const double* __restri
 template <class ST>
 __global__ __launch_bounds__(64) void k_tridiag_psi(Dims d, const double* __restrict__ tri,
                                                    SPtr3<ST> spec, SPtr3<ST> spec2, double3 plo,
-                                                   double3 phi_) {
+                                                   double3 phi_, const int* gate) {
+    if (gate && *gate) return;
     const ModeLane ml = mode_lane(d, tri);
     const int c = blockIdx.y;
     const ST* col = spec.p[c] + ml.off;
@@ -968,12 +969,12 @@ __global__ __launch_bounds__(1024) void k_check(const double* __restrict__ parti
 // Convergence checks of the two flow solves of a step in one launch (flow_check.h); one block
 // per instance.
 template <bool BATCH>
-__global__ __launch_bounds__(1024) void k_check_flow(int nblocks, int last_cycle, ChkArgs one,
+__global__ __launch_bounds__(1024) void k_check_flow(int nblocks, int mode, ChkArgs one,
                                                     const ChkArgs* __restrict__ tab) {
     const ChkArgs& a = inst_args<BATCH>(one, tab, (int)blockIdx.x);
     if (a.gate && *a.gate) return;
     __shared__ double sh[4 * 16];
-    flow_check_block(a.part, nblocks, a.rtol, a.scal, a.istat, sh, last_cycle, a.log);
+    flow_check_block(a.part, nblocks, a.rtol, a.scal, a.istat, sh, mode, a.log);
 }
 
 }  // namespace
@@ -1100,14 +1101,14 @@ void launch_tri_pair(hipStream_t s, const Dims& d, bool f32, bool corr, const Ov
     void* const sp2[3] = {t.spec2[0], t.spec2[1], t.spec2[2]};
     if (f32) {
         launch_kernel(k_tridiag_y<float>, grid, dim3(64), 0, s, d, t.triw, sptr<float>(sp, 3),
-                      (const int*)nullptr, scale, olo, ohi);
+                      t.gate, scale, olo, ohi);
         launch_kernel(k_tridiag_psi<float>, grid, dim3(64), 0, s, d, t.tri, sptr<float>(sp, 3),
-                      sptr<float>(sp2, 3), lo, hi);
+                      sptr<float>(sp2, 3), lo, hi, t.gate);
     } else {
         launch_kernel(k_tridiag_y<double>, grid, dim3(64), 0, s, d, t.triw, sptr<double>(sp, 3),
-                      (const int*)nullptr, scale, olo, ohi);
+                      t.gate, scale, olo, ohi);
         launch_kernel(k_tridiag_psi<double>, grid, dim3(64), 0, s, d, t.tri, sptr<double>(sp, 3),
-                      sptr<double>(sp2, 3), lo, hi);
+                      sptr<double>(sp2, 3), lo, hi, t.gate);
     }
 }
 
@@ -1218,13 +1219,13 @@ void launch_resid_flow(hipStream_t s, const Dims& d, const double* const om[3],
     launch_resid_flow_over(s, d, false, over_one(r));
 }
 
-void launch_check_flow_over(hipStream_t s, const Dims& d, int last_cycle, const Over<ChkArgs>& a) {
+void launch_check_flow_over(hipStream_t s, const Dims& d, int mode, const Over<ChkArgs>& a) {
     const unsigned ni = a.tab ? (unsigned)a.n : 1u;
     const int nb = resid_flow_blocks(d);
     if (a.tab)
-        launch_kernel(k_check_flow<true>, dim3(ni), dim3(1024), 0, s, nb, last_cycle, a.one, a.tab);
+        launch_kernel(k_check_flow<true>, dim3(ni), dim3(1024), 0, s, nb, mode, a.one, a.tab);
     else
-        launch_kernel(k_check_flow<false>, dim3(1), dim3(1024), 0, s, nb, last_cycle, a.one, a.tab);
+        launch_kernel(k_check_flow<false>, dim3(1), dim3(1024), 0, s, nb, mode, a.one, a.tab);
 }
 
 void launch_check_flow(hipStream_t s, const Dims& d, const double* partials, double rtol,
@@ -1234,7 +1235,7 @@ void launch_check_flow(hipStream_t s, const Dims& d, const double* partials, dou
     c.scal = scal;
     c.istat = istat;
     c.rtol = rtol;
-    launch_check_flow_over(s, d, 1, over_one(c));
+    launch_check_flow_over(s, d, CK_LAST, over_one(c));
 }
 
 void launch_check(hipStream_t s, const double* partials, int nblocks, double rtol, int cycle,

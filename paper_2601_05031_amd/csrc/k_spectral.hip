@@ -681,8 +681,8 @@ __device__ __forceinline__ void plane_hartley(T* __restrict__ P, const tw2v* __r
 
 // ZFIRST (the source's forward transform): z then x, from the field z.spec[c] (FP64, the
 // interior rows) into the spectral buffer x.spec[c]. Otherwise (the inverse of the omega and
-// psi modes): x then z, from x.spec[c] into the field z.u[c]. FP64 only; no gate, no
-// accumulation. Persistent: block b takes the planes b, b + G, ... (G = gridDim.x; plane
+// psi modes): x then z, from x.spec[c] into the field z.u[c]. FP64 only, no accumulation; planes
+// of an instance whose z.gate is set are skipped. Persistent: block b takes the planes b, b + G, ... (G = gridDim.x; plane
 // p = (instance * NC + component) * M + j - 1) and keeps the loads of its next plane in flight
 // in registers while it works on the current one: the first half (NR1 values per lane) during
 // the transforms, the rest during the stores (the whole plane beside a transform pass would
@@ -729,6 +729,17 @@ __global__ __launch_bounds__(kPlaneThreads) void k_hxz_plane(Dims d, ZArgs zone,
         const HxArgs& xa = inst_args<BATCH>(xone, xtab, inst);
         return (Gl<double>*)(ZFIRST ? pick(xa.spec, c) : pick(za.u, c)) + (size_t)j * NZ;
     };
+    // the next plane from q on (stride: the grid) whose instance is not gated off
+    auto live = [&](int q) {
+        while (q < nplanes) {
+            const int inst = BATCH ? q / (d.M * NC) : 0;
+            const ZArgs& za = inst_args<BATCH>(zone, ztab, inst);
+            if (!(za.gate && *(const Gl<int>*)za.gate)) break;
+            if (!BATCH) return nplanes;
+            q += (int)gridDim.x;
+        }
+        return q;
+    };
     // x-row i of a plane at P[i * RS]; 16-byte values, NZ / 2 per row
     constexpr int NR1 = (NR + 1) / 2;
     double2 v[NR];
@@ -742,7 +753,7 @@ __global__ __launch_bounds__(kPlaneThreads) void k_hxz_plane(Dims d, ZArgs zone,
             v[r] = ldg2(in + i * pstride + 2 * k2);
         }
     };
-    int p = blockIdx.x;
+    int p = live(blockIdx.x);
     if (p < nplanes) load(p, 0, NR);
     while (p < nplanes) {
 #pragma unroll
@@ -754,7 +765,7 @@ __global__ __launch_bounds__(kPlaneThreads) void k_hxz_plane(Dims d, ZArgs zone,
             }
         }
         __syncthreads();
-        const int pn = p + (int)gridDim.x;
+        const int pn = BATCH ? live(p + (int)gridDim.x) : p + (int)gridDim.x;
         if (pn < nplanes) load(pn, 0, NR1);   // in flight while this plane is transformed
         // the lane index through an empty asm statement: the transforms' LDS offsets are then
         // recomputed in every round instead of held (and spilled) across the loop
@@ -1116,7 +1127,7 @@ bool plane_fits(const Dims& d) {
 bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,
                   const Over<HxArgs>& x) {
     if (!plane_fits(d) || (ncomp != 3 && ncomp != 6)) return false;
-    if (z.one.gate || z.one.add || x.one.gate) return false;
+    if (z.one.add) return false;
     const bool batch = z.tab != nullptr;
     if (batch != (x.tab != nullptr) || (batch && z.n != x.n)) return false;
     const int ni = batch ? z.n : 1;

@@ -394,15 +394,15 @@ void enqueue_cycle(vs_state* S, const RhsArgs& rhs, double* const u[3], int ncom
     });
 }
 
-// Verified solve: cycle 0, then up to max_cycles-1 correction cycles gated on the device flag
-// (a cycle runs only while the previous check missed rtol); each cycle ends with a check.
-// warm = 1: cycle 0 too solves for the correction of the residual of the incoming u (the
-// refined mode's defect correction from the previous time step's field).
+// Verified solve: the cycles first .. max_cycles-1. Cycle 0 solves directly; the correction
+// cycles are gated on the device flag (a cycle runs only while the previous check missed rtol);
+// each cycle ends with a check. stop < max_cycles leaves the cycles from stop on to the caller
+// (who reads IS_CONV first).
 void enqueue_solve(vs_state* S, const RhsArgs& rhs, double* const u[3], int ncomp, double rtol,
-                   int max_cycles, int tag, int warm = 0) {
-    for (int cyc = 0; cyc < max_cycles; ++cyc) {
+                   int max_cycles, int tag, int first, int stop) {
+    for (int cyc = first; cyc < stop; ++cyc) {
         const int* gate = cyc == 0 ? nullptr : S->istat + IS_CONV;
-        enqueue_cycle(S, rhs, u, ncomp, (cyc > 0 || warm) ? 1 : 0, tag, gate);
+        enqueue_cycle(S, rhs, u, ncomp, cyc > 0 ? 1 : 0, tag, gate);
         enqueue_verify(S, rhs, u, ncomp, rtol, cyc, cyc == max_cycles - 1, tag, gate);
     }
 }
@@ -442,9 +442,11 @@ bool refined_fused(const vs_state* S) { return S->f32 && fused_flow_ok(S->d); }
 
 // Arguments of one step of S that reads phi[par] and writes phi[1 - par] (par = -1: the
 // initial state, phi[0] read in place: no advance). with_ck: the advance takes the previous
-// step's flow check. dt = 0: the initial solve.
-StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
+// step's flow check. dt = 0: the initial solve. halt: FP64 steps that may take correction
+// cycles (poisson_max_cycles > 1): a check that misses rtol halts the call's later kernels.
+StepArgs step_args(vs_state* S, int par, double dt, bool with_ck, bool halt) {
     StepArgs A{};
+    const int* hgate = halt ? S->istat + IS_HALT : nullptr;
     const double* phi_in = S->phi[par < 0 ? 0 : par];
     double* phi_new = par < 0 ? S->phi[0] : S->phi[1 - par];
     const double a = (S->p.rho > 0.0 && dt > 0.0) ? S->p.rho / (S->p.eta * dt) : 0.0;
@@ -463,10 +465,12 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
         ad.ck_istat = S->istat;
         ad.ck_rtol = S->p.poisson_rtol;
         ad.ck_nb = resid_flow_blocks(S->d);
+        ad.ck_mode = halt ? CK_HALT : CK_LAST;
         ad.ck_log = S->log;
     }
+    ad.gate = hgate;
     A.adv = over_one(ad);
-    A.va = over_one(VaArgs{phi_new, S->part, S->p.eps});
+    A.va = over_one(VaArgs{phi_new, S->part, S->p.eps, hgate});
     MuArgs m{};
     m.phi = phi_new;
     m.mu = S->mu;
@@ -481,6 +485,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
     m.eps = S->p.eps;
     m.sigma = S->p.sigma;
     m.init = par < 0 ? 1 : 0;
+    m.gate = hgate;
     A.mu = over_one(m);
     SrcArgs sr{};
     sr.phi = phi_new;
@@ -491,6 +496,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
     }
     sr.inv_eta = 1.0 / S->p.eta;
     sr.a = a;
+    sr.gate = hgate;
     A.src = over_one(sr);
     ZArgs zf{};
     for (int c = 0; c < 3; ++c) {
@@ -498,6 +504,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
         zf.u[c] = (double*)S->spec[c];
     }
     zf.tw = S->twz;
+    zf.gate = hgate;
     A.zfwd = over_one(zf);
     HxArgs h3{}, h6{};
     for (int c = 0; c < 3; ++c) {
@@ -506,6 +513,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
         h6.spec[3 + c] = S->spec2[c];
     }
     h3.tw = h6.tw = S->twx;
+    h3.gate = h6.gate = hgate;
     A.hx3 = over_one(h3);
     A.hx6 = over_one(h6);
     TriArgs t{};
@@ -519,6 +527,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
         t.plo[c] = S->psi_wall_lo[c];
         t.phi[c] = S->psi_wall_hi[c];
     }
+    t.gate = hgate;
     A.tri = over_one(t);
     ZArgs z6{};
     for (int c = 0; c < 3; ++c) {
@@ -528,6 +537,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
         z6.u[3 + c] = S->ps[c];
     }
     z6.tw = S->twz;
+    z6.gate = hgate;
     A.zout6 = over_one(z6);
     ResArgs r{};
     for (int c = 0; c < 3; ++c) {
@@ -537,6 +547,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
     }
     r.part = S->part;
     r.ashift = a;
+    r.gate = hgate;
     A.res = over_one(r);
     ChkArgs ck{};
     ck.part = S->part;
@@ -544,6 +555,7 @@ StepArgs step_args(vs_state* S, int par, double dt, bool with_ck) {
     ck.istat = S->istat;
     ck.rtol = S->p.poisson_rtol;
     ck.log = S->log;
+    ck.gate = hgate;
     A.chk = over_one(ck);
     // the refined mode's predictor (steps only, not the initial solve): increments i1 = inc[par]
     // (the last step's) and i2 = inc[1 - par] (the one before), which the first cycle's update
@@ -615,15 +627,12 @@ struct StepCfg {
     Dims d;
     FftPlan px, pz;
     bool f32;
-    int model, mc;
-    double rtol;
-    bool inertial;
+    int model;
     vs_state* timer;   // null: no timing
 };
 
 StepCfg step_cfg(vs_state* S) {
-    return StepCfg{S->stream, S->d, S->px, S->pz, S->f32, S->p.model, S->p.poisson_max_cycles,
-                   S->p.poisson_rtol, S->p.rho > 0.0, S->prof_on ? S : nullptr};
+    return StepCfg{S->stream, S->d, S->px, S->pz, S->f32, S->p.model, S->prof_on ? S : nullptr};
 }
 
 template <class F>
@@ -647,9 +656,11 @@ void enqueue_va_mu_args(const StepCfg& c, const StepArgs& A) {
 // defect-correction cycles from the incoming fields, each a residual pass in FP64 whose result
 // is transformed and solved in FP32 and added to the FP64 fields, then verified; cycles after
 // the first are gated on the device flag of the previous check.
-// max_cycles > 1 in FP64: the verification is left to enqueue_fp64_corrections.
+// verify = false in FP64: the verification is left to enqueue_fp64_corrections. ck: the
+// CheckMode of the FP64 check.
 // Returns true when the final check was left to the next step's advance (defer).
-bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_cycles) {
+bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_cycles, int ck,
+                       bool verify = true) {
     timed_cfg(c, K_SOURCE, [&] { launch_source(c.st, c.d, c.f32 ? P32 : P64, A.src); });
     if (c.f32) {
         // the transforms of a cycle as two FP32 plane passes where the plane fits in LDS
@@ -673,7 +684,7 @@ bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_
             timed_cfg(c, K_RESID_FLOW, [&] { launch_resid_flow_over(c.st, c.d, false, A.resc[g]); });
             if (max_cycles == 1 && defer) return true;
             timed_cfg(c, K_CHECK, [&] {
-                launch_check_flow_over(c.st, c.d, cyc == max_cycles - 1 ? 1 : 0, A.chkc[g]);
+                launch_check_flow_over(c.st, c.d, cyc == max_cycles - 1 ? CK_LAST : CK_GATED, A.chkc[g]);
             });
         }
         return false;
@@ -696,17 +707,25 @@ bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_
         timed_cfg(c, K_DHT_X_PAIR, [&] { launch_hx(c.st, c.d, c.px, false, 6, A.hx6); });
         timed_cfg(c, K_DHT_Z_OUT_PAIR, [&] { launch_hz(c.st, c.d, c.pz, false, 6, A.zout6); });
     }
-    if (max_cycles > 1) return false;
+    if (!verify) return false;
     // both residuals in one pass, then both checks in one launch, or, when another step
     // follows in the same call, in the first block of its advance kernel
     timed_cfg(c, K_RESID_FLOW, [&] { launch_resid_flow_over(c.st, c.d, false, A.res); });
     if (defer) return true;
-    timed_cfg(c, K_CHECK, [&] { launch_check_flow_over(c.st, c.d, 1, A.chk); });
+    timed_cfg(c, K_CHECK, [&] { launch_check_flow_over(c.st, c.d, ck, A.chk); });
     return false;
 }
 
-// FP64 correction cycles after the direct pass (poisson_max_cycles > 1), per solve, through
-// the general verified path (normally never needed: the direct pass is exact).
+// FP64 with poisson_max_cycles > 1. The direct pass meets any reachable rtol, so the correction
+// cycles are not enqueued with the step (32 launches that would each find the convergence flag
+// set and exit, about 4 us apiece: 125 of 322 us per step at 128^3, 130 of 145 us at 64^3).
+// The steps of a call run as those of max_cycles = 1, every kernel gated on IS_HALT; a check
+// that misses rtol sets it, so the state stays as that step's direct pass left it, and the
+// host, at the call's end, takes that step's corrections (enqueue_fp64_corrections) and the
+// remaining steps of the call with their corrections in line (collect).
+bool halting(const vs_state* S) { return !S->f32 && S->p.poisson_max_cycles > 1; }
+
+// Correction cycles after the direct pass, per solve, through the general verified path.
 void enqueue_fp64_corrections(vs_state* S) {
     const double rtol = S->p.poisson_rtol;
     const int mc = S->p.poisson_max_cycles;
@@ -735,32 +754,27 @@ void enqueue_fp64_corrections(vs_state* S) {
 // for a full solve (its FP32 cycles each gain about six digits).
 void enqueue_init(vs_state* S) {
     const StepCfg c = step_cfg(S);
-    const StepArgs A = step_args(S, -1, 0.0, false);
+    const bool halt = halting(S);
+    const StepArgs A = step_args(S, -1, 0.0, false, halt);
     enqueue_va_mu_args(c, A);
-    if (S->f32) {
-        enqueue_flow_args(c, A, false, S->p.poisson_max_cycles > 4 ? S->p.poisson_max_cycles : 4);
-        return;
-    }
-    enqueue_flow_args(c, A, false, S->p.poisson_max_cycles);
-    if (S->p.poisson_max_cycles > 1) enqueue_fp64_corrections(S);
+    enqueue_flow_args(c, A, false, S->p.poisson_max_cycles > 4 ? S->p.poisson_max_cycles : 4,
+                      halt ? CK_HALT : CK_LAST);
 }
 
 // One time step. more_follow: another step of the same call comes after this one, so its
-// advance kernel can take this step's flow check.
-void enqueue_step(vs_state* S, double dt, bool more_follow) {
+// advance kernel can take this step's flow check. inline_corr: FP64 correction cycles enqueued
+// with the step (the steps after a halt).
+void enqueue_step(vs_state* S, double dt, bool more_follow, bool inline_corr = false) {
     const StepCfg c = step_cfg(S);
-    const StepArgs A = step_args(S, S->cur, dt, S->check_pending);
+    const bool halt = halting(S) && !inline_corr;
+    const StepArgs A = step_args(S, S->cur, dt, S->check_pending, halt);
     S->check_pending = false;
     timed_cfg(c, K_ADVANCE, [&] { launch_advance(c.st, c.d, c.f32 ? P32 : P64, A.adv); });
     S->cur = 1 - S->cur;
     enqueue_va_mu_args(c, A);
-    const int mc = S->p.poisson_max_cycles;
-    if (S->f32) {
-        S->check_pending = enqueue_flow_args(c, A, more_follow, mc);
-        return;
-    }
-    S->check_pending = enqueue_flow_args(c, A, more_follow && mc == 1, mc);
-    if (mc > 1) enqueue_fp64_corrections(S);
+    S->check_pending = enqueue_flow_args(c, A, more_follow && !inline_corr, S->p.poisson_max_cycles,
+                                         halt ? CK_HALT : CK_LAST, !inline_corr);
+    if (inline_corr) enqueue_fp64_corrections(S);
 }
 
 // The inertial variant's vorticity pivots depend on dt (a = rho/(eta dt)): made on the host
@@ -831,10 +845,22 @@ vs_status read_status(vs_state* S, double* sc, int* ist) {
     return VS_OK;
 }
 
-vs_status collect(vs_state* S, const char* what) {
+// Waits for a call that enqueued nsteps steps of dt from phi[cur0] (nsteps = 0: the initial
+// solve) and maps the device flags to a status. Where a check halted the call at step k, the
+// fields are those of step k's direct pass: its correction cycles are taken first, then steps
+// k+1 .. nsteps with theirs in line.
+vs_status collect(vs_state* S, const char* what, double dt, int nsteps, int cur0) {
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
-    const vs_status rs = read_status(S, sc, ist);
+    vs_status rs = read_status(S, sc, ist);
+    if (rs == VS_OK && ist[IS_HALT]) {
+        const int k = nsteps ? ist[IS_PASSED] + 1 : 0;
+        S->cur = (cur0 + k) & 1;
+        enqueue_fp64_corrections(S);
+        for (int s = k; s < nsteps; ++s) enqueue_step(S, dt, false, true);
+        HIP_TRY(hipGetLastError());
+        rs = read_status(S, sc, ist);
+    }
     if (rs != VS_OK) return rs;
     S->gamma_host = sc[SC_GAMMA];
     S->last_relres = sc[SC_RELRES_MAX];
@@ -1016,7 +1042,7 @@ vs_status vs_init(const vs_grid* grid, const vs_walls* walls, const vs_params* p
     INIT_TRY(hipGetLastError());
     enqueue_init(S);
     INIT_TRY(hipGetLastError());
-    st = collect(S, "vs_init");
+    st = collect(S, "vs_init", 0.0, 0, 0);
     if (st != VS_OK) return bail(st);
 #undef INIT_TRY
     *out = S;
@@ -1034,11 +1060,18 @@ vs_status vs_poisson_solve(vs_state* S, const double* f, double* u, double rtol,
     r.mode = RHS_FIELD;
     r.f[0] = f;
     double* const uu[3] = {u, nullptr, nullptr};
-    enqueue_solve(S, r, uu, 1, rtol, max_cycles, TAG_FIELD);
+    // the direct cycle almost always meets rtol: the correction cycles (seven launches each,
+    // which would all exit at once) are enqueued only after its check missed
+    enqueue_solve(S, r, uu, 1, rtol, max_cycles, TAG_FIELD, 0, 1);
     HIP_TRY(hipGetLastError());
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
-    const vs_status rs = read_status(S, sc, ist);
+    vs_status rs = read_status(S, sc, ist);
+    if (rs == VS_OK && !ist[IS_CONV] && max_cycles > 1) {
+        enqueue_solve(S, r, uu, 1, rtol, max_cycles, TAG_FIELD, 1, max_cycles);
+        HIP_TRY(hipGetLastError());
+        rs = read_status(S, sc, ist);
+    }
     if (rs != VS_OK) return rs;
     if (cycles_out) *cycles_out = ist[IS_CYCLES];
     if (relres_out) *relres_out = sc[SC_RELRES_LAST];
@@ -1174,12 +1207,18 @@ vs_status vs_poisson_solve_noalloc(const vs_grid* grid, const double* f, double*
     r.mode = RHS_FIELD;
     r.f[0] = f;
     double* const uu[3] = {u, nullptr, nullptr};
-    enqueue_solve(&S, r, uu, 1, rtol, max_cycles, TAG_FIELD);
+    enqueue_solve(&S, r, uu, 1, rtol, max_cycles, TAG_FIELD, 0, 1);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(hs));
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
     HIP_TRY(hipMemcpy(ist, S.istat, sizeof ist, hipMemcpyDeviceToHost));
+    if (!ist[IS_CONV] && max_cycles > 1) {
+        enqueue_solve(&S, r, uu, 1, rtol, max_cycles, TAG_FIELD, 1, max_cycles);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(hs));
+        HIP_TRY(hipMemcpy(ist, S.istat, sizeof ist, hipMemcpyDeviceToHost));
+    }
     HIP_TRY(hipMemcpy(sc, S.scal, sizeof sc, hipMemcpyDeviceToHost));
     if (cycles_out) *cycles_out = ist[IS_CYCLES];
     if (relres_out) *relres_out = sc[SC_RELRES_LAST];
@@ -1204,23 +1243,22 @@ vs_status vs_step(vs_state* S, double dt, int32_t nsteps) {
     vs_status st = ensure_inertial_table(S, dt);
     if (st != VS_OK) return st;
     timed(S, K_RESET, [&] { launch_reset_stats(S->stream, S->scal, S->istat); });
+    const int cur0 = S->cur;
     for (int s = 0; s < nsteps; ++s) enqueue_step(S, dt, s + 1 < nsteps);
     HIP_TRY(hipGetLastError());
     S->step += nsteps;
-    const vs_status cs = collect(S, "vs_step");
+    const vs_status cs = collect(S, "vs_step", dt, nsteps, cur0);
     print_log(S);
     return cs;
 }
 
-vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* adj_prev,
-                       double dparams[2]) {
-    if (!S) return fail(VS_E_STATE, "state is NULL");
-    if (!adj_next || !adj_prev || !dparams) return fail(VS_E_ARG, "adj_next, adj_prev and dparams are required");
-    if (adj_next == adj_prev) return fail(VS_E_ARG, "adj_next and adj_prev must not alias");
-    if (!(dt > 0.0) || !std::isfinite(dt)) return fail(VS_E_ARG, "dt must be > 0");
-    if (S->f32) return fail(VS_E_UNSUPPORTED, "vs_grad_step: the reverse step runs in the FP64 mode only");
-    if (S->p.rho > 0.0)
-        return fail(VS_E_UNSUPPORTED, "vs_grad_step: no reverse step for the inertial variant");
+}  // extern "C"
+
+namespace {
+
+// The kernels of one reverse step. one_pass: both adjoint solves in one verified spectral pass
+// (no correction cycles); otherwise each through the general path with its correction cycles.
+void enqueue_grad(vs_state* S, double dt, const double* adj_next, double* adj_prev, bool one_pass) {
     const Dims& d = S->d;
     hipStream_t st = S->stream;
     const double rtol = S->p.poisson_rtol;
@@ -1237,13 +1275,13 @@ vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* a
     // advection, L_h mu and lambda_V terms; q = psi_bar
     timed(S, K_ADJ_ADVECT, [&] {
         launch_adj_advect(st, d, adj_next, phi, cps, dt, S->p.mobility, S->vz_lo, S->vz_hi,
-                          adj_prev, mubar, q, S->part, S->scal, S->istat, mc == 1 ? w6 : nullptr);
+                          adj_prev, mubar, q, S->part, S->scal, S->istat, one_pass ? w6 : nullptr);
     });
     // psi_int = P(-omega_int; psi walls): first adjoint solve, homogeneous walls;
     // omega_int = P(S; omega walls): second adjoint solve, of -u1, giving S_bar
     double* sb[3] = {q[0], q[1], q[2]};          // S_bar
     const double* u1w[3] = {nullptr, nullptr, nullptr};   // u1 for the source kernel's wall term
-    if (mc == 1) {
+    if (one_pass) {
         // one verified pass, as the forward flow solve: q transformed once, u1's modes solved
         // and S_bar's from them in the pair kernel (zero walls), both inverse-transformed in
         // place in the two spectral sets (u1 in spec, S_bar in spec2), then both residuals
@@ -1301,13 +1339,13 @@ vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* a
         RhsArgs r1{};
         r1.mode = RHS_FIELD;
         for (int c = 0; c < 3; ++c) r1.f[c] = q[c];
-        enqueue_solve(S, r1, u1, 3, rtol, mc, TAG_FIELD);
+        enqueue_solve(S, r1, u1, 3, rtol, mc, TAG_FIELD, 0, mc);
         timed(S, K_ADJ_WALLS, [&] { launch_adj_wall_couple(st, d, u1, S->ps, S->part, S->scal, SC_ADJ_PSIC); });
         launch_zero_walls(st, d, q, 3);
         RhsArgs r2{};
         r2.mode = RHS_NEGW;
         for (int c = 0; c < 3; ++c) r2.f[c] = u1[c];
-        enqueue_solve(S, r2, q, 3, rtol, mc, TAG_FIELD);
+        enqueue_solve(S, r2, q, 3, rtol, mc, TAG_FIELD, 0, mc);
     }
     // S = (1/eta) D phi x D mu; the wall couplings of the adjoint solves as block partials
     const double* const cpsw[3] = {S->ps[0], S->ps[1], S->ps[2]};
@@ -1315,7 +1353,7 @@ vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* a
     timed(S, K_ADJ_SOURCE, [&] {
         launch_adj_source(st, d, phi, S->mu, sb, 1.0 / S->p.eta, adj_prev, mubar,
                           u1w[0] ? u1w : nullptr, cpsw, comw, S->part,
-                          mc == 1 ? S->part : nullptr, rtol, S->scal, S->istat);
+                          one_pass ? S->part : nullptr, rtol, S->scal, S->istat);
     });
     // mu(phi)
     double* gbar = (double*)S->spec[0];
@@ -1331,10 +1369,34 @@ vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* a
                        dt, S->p.mobility, S->p.rate_V, S->p.k_A, adj_prev, S->part,
                        S->p.model == VS_BENDING, u1w[0] != nullptr, S->scal);
     });
+}
+
+}  // namespace
+
+extern "C" {
+
+vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* adj_prev,
+                       double dparams[2]) {
+    if (!S) return fail(VS_E_STATE, "state is NULL");
+    if (!adj_next || !adj_prev || !dparams) return fail(VS_E_ARG, "adj_next, adj_prev and dparams are required");
+    if (adj_next == adj_prev) return fail(VS_E_ARG, "adj_next and adj_prev must not alias");
+    if (!(dt > 0.0) || !std::isfinite(dt)) return fail(VS_E_ARG, "dt must be > 0");
+    if (S->f32) return fail(VS_E_UNSUPPORTED, "vs_grad_step: the reverse step runs in the FP64 mode only");
+    if (S->p.rho > 0.0)
+        return fail(VS_E_UNSUPPORTED, "vs_grad_step: no reverse step for the inertial variant");
+    const double rtol = S->p.poisson_rtol;
+    enqueue_grad(S, dt, adj_next, adj_prev, true);
     HIP_TRY(hipGetLastError());
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
-    const vs_status rs = read_status(S, sc, ist);
+    vs_status rs = read_status(S, sc, ist);
+    if (rs == VS_OK && (ist[IS_FLAGS] & ST_NOCONV) && S->p.poisson_max_cycles > 1) {
+        // the one pass missed rtol: the whole reverse step again (its inputs are untouched) with
+        // the correction cycles
+        enqueue_grad(S, dt, adj_next, adj_prev, false);
+        HIP_TRY(hipGetLastError());
+        rs = read_status(S, sc, ist);
+    }
     if (rs != VS_OK) return rs;
     if (ist[IS_FLAGS] & ST_NONFINITE) return fail(VS_E_NONFINITE, "vs_grad_step: non-finite residual");
     if (ist[IS_FLAGS] & ST_NOCONV)
@@ -1592,7 +1654,7 @@ vs_status autotune_state(vs_state* S, Tuning* picked) {
     HIP_TRY(hipMemcpyAsync(S->src[2], S->mu, fbytes, hipMemcpyDeviceToDevice, S->stream));
     const StepCfg c = step_cfg(S);
     const double dt = 1e-12;   // the advance's output buffer is scratch; any dt does
-    const StepArgs A = step_args(S, S->cur, dt, false);
+    const StepArgs A = step_args(S, S->cur, dt, false, false);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     HIP_TRY(hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -1746,8 +1808,10 @@ extern "C" vs_status vs_autotune(vs_state* S, int32_t picked[7]) {
 // class against 1.05e10 with groups of about 2^21 nodes (which kept more of each hand-off in
 // the 256 MB Infinity Cache). Two steps of every class are captured into one HIP graph (two
 // steps bring every instance's phi buffer back to where it started), the classes spread over
-// the batch streams, and replayed. Instances outside the fused forms (FP64 with more than one
-// cycle per solve) are stepped one by one inside the same graph.
+// the batch streams, and replayed. An FP64 instance with more than one cycle per solve whose
+// check misses rtol halts alone (its blocks exit); the host finishes its steps after the replays.
+// Instances outside the fused forms (grids without them) are stepped one by one inside the same
+// graph.
 struct BatchClass {
     Dims d{};
     FftPlan px{}, pz{};
@@ -1788,9 +1852,7 @@ bool same_class(const vs_state* a, const vs_state* b) {
            a->p.poisson_max_cycles == b->p.poisson_max_cycles;
 }
 
-bool class_eligible(const vs_state* S) {
-    return fused_flow_ok(S->d) && (S->f32 || S->p.poisson_max_cycles == 1);
-}
+bool class_eligible(const vs_state* S) { return fused_flow_ok(S->d); }
 
 
 double batch_dt(const vs_batch* B, const vs_state* S, const double* dt) {
@@ -1817,7 +1879,8 @@ vs_status build_tables(vs_batch* B, const double* dt) {
             std::vector<StepArgs> per;
             for (vs_state* S : C.st) {
                 const int par = (S->cur + k) & 1;
-                per.push_back(step_args(S, par, batch_dt(B, S, dt), k == 1 && C.mc == 1));
+                const bool with_ck = k == 1 && (C.mc == 1 || !C.f32);
+                per.push_back(step_args(S, par, batch_dt(B, S, dt), with_ck, halting(S)));
             }
             StepArgs& A = C.A[k];
 #define VS_GATHER(F)                                                                        \
@@ -1857,11 +1920,11 @@ vs_status build_tables(vs_batch* B, const double* dt) {
 
 // One step of a class: every kernel launched once over the class's tables.
 void enqueue_class_step(const BatchClass& C, int k, hipStream_t st) {
-    const StepCfg c{st, C.d, C.px, C.pz, C.f32, C.model, C.mc, 0.0, false, nullptr};
+    const StepCfg c{st, C.d, C.px, C.pz, C.f32, C.model, nullptr};
     const StepArgs& A = C.A[k];
     launch_advance(st, C.d, C.f32 ? P32 : P64, A.adv);
     enqueue_va_mu_args(c, A);
-    enqueue_flow_args(c, A, k == 0 && C.mc == 1, C.mc);
+    enqueue_flow_args(c, A, k == 0, C.mc, !C.f32 && C.mc > 1 ? CK_HALT : CK_LAST);
 }
 
 // Capture two time steps of every class and loose instance: fork from the capture stream to
@@ -2029,8 +2092,9 @@ vs_status vs_batch_step(vs_batch* B, const double* dt, int32_t nsteps) {
     HIP_TRY(hipStreamSynchronize(B->origin));
     vs_status worst = VS_OK;
     for (size_t i = 0; i < n; ++i) {
-        B->st[i]->step += nsteps;
-        const vs_status st = collect(B->st[i], "vs_batch_step");
+        vs_state* S = B->st[i];
+        S->step += nsteps;
+        const vs_status st = collect(S, "vs_batch_step", dt[i], nsteps, S->cur);
         if (st != VS_OK && worst == VS_OK) worst = st;
     }
     return worst;

@@ -85,9 +85,18 @@ enum {
     IS_HIST = 3,              // refined mode: time increments of omega and psi the predictor
                               // holds (0, 1, 2), slots 3 and 4 by the parity of the step
     IS_LOGN = 5,              // records written to the per-step log since vs_init
+    IS_HALT = 6,              // a step's direct solve missed rtol: the call's later kernels exit
+    IS_PASSED = 7,            // steps whose check passed since the last reset (CK_HALT checks)
     IS_NSTAT = 16
 };
 enum { ST_NOCONV = 1, ST_NONFINITE = 2 };
+// What a flow check does when a solve missed rtol.
+enum CheckMode {
+    CK_GATED = 0,             // later correction cycles run, gated on IS_CONV
+    CK_LAST = 1,              // the last cycle: ST_NOCONV
+    CK_HALT = 2               // IS_HALT: every later kernel of the call exits at once and the
+                              // host takes the correction cycles of this step
+};
 // The per-step log: a ring of kLogCap records of kLogFields doubles (VS_L_* in include/vs.h),
 // one per time step (and one for the initial solve), written by the step's final flow check.
 constexpr int kLogCap = VS_LOG_CAP;
@@ -178,7 +187,9 @@ struct AdvArgs {
     int* ck_istat;
     double ck_rtol;
     int ck_nb;               // residual partial blocks of that check
+    int ck_mode;             // CheckMode of that check
     double* ck_log;          // the per-step log that check appends to
+    const int* gate;         // skip when *gate != 0 (a halted call), or null
 };
 void launch_advance(hipStream_t s, const Dims& d, Prec pr, const Over<AdvArgs>& a);
 int resid_flow_blocks(const Dims& d);
@@ -187,6 +198,7 @@ struct VaArgs {
     const double* phi;
     double* part;
     double eps;
+    const int* gate;
 };
 void launch_va_partials(hipStream_t s, const Dims& d, const Over<VaArgs>& a);
 int va_partial_blocks(const Dims& d);
@@ -203,6 +215,7 @@ struct MuArgs {
     int* istat;
     double rate_V, k_A, gamma0, mob, C_b, eps, sigma;
     int init;
+    const int* gate;
 };
 void launch_mu(hipStream_t s, const Dims& d, int model, Prec pr, const Over<MuArgs>& a);
 
@@ -214,6 +227,7 @@ struct SrcArgs {
     void* src[3];
     const double* om[3];
     double inv_eta, a;
+    const int* gate;
 };
 void launch_source(hipStream_t s, const Dims& d, Prec pr, const Over<SrcArgs>& a);
 
@@ -314,8 +328,8 @@ bool fused_flow_ok(const Dims& d);
 // Both transform directions in one pass per (interior row, component), the (x, z) plane in
 // LDS: zfirst, z then x from z.spec into x.spec (the source's forward transform); otherwise x
 // then z from x.spec into z.u (the inverse of the omega and psi modes). FP64 spectral data,
-// n_x = n_z in {32, 48, 64, 96, 128}, no gate or accumulation; returns false (nothing
-// launched) otherwise.
+// n_x = n_z in {32, 48, 64, 96, 128}, no accumulation, gated per instance by z.gate; returns
+// false (nothing launched) otherwise.
 bool plane_fits(const Dims& d);
 bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,
                   const Over<HxArgs>& x);
@@ -327,8 +341,8 @@ void launch_hx(hipStream_t s, const Dims& d, const FftPlan& px, bool f32, int nc
 void launch_tri_pair(hipStream_t s, const Dims& d, bool f32, bool corr, const Over<TriArgs>& a);
 // f32src: S stored as float (the refined mode).
 void launch_resid_flow_over(hipStream_t s, const Dims& d, bool f32src, const Over<ResArgs>& a);
-// last_cycle = 0: a defect-correction cycle that may be followed by another (gated).
-void launch_check_flow_over(hipStream_t s, const Dims& d, int last_cycle, const Over<ChkArgs>& a);
+// mode: a CheckMode.
+void launch_check_flow_over(hipStream_t s, const Dims& d, int mode, const Over<ChkArgs>& a);
 
 // Single-instance forms of the same passes (vs_poisson_solve, refinement cycles, the reverse
 // step).

@@ -1,0 +1,149 @@
+"""FP64 steps with correction cycles allowed (poisson_max_cycles > 1): the cycles are enqueued only
+after a step's check missed rtol. The call's later kernels then exit, the host takes that step's
+cycles and finishes the call. rtol is placed between the residuals of an uncorrected run, so that
+the first steps pass and a chosen later one misses."""
+import numpy as np
+import pytest
+
+from workloads import workload
+from workloads.shapes import GridSpec
+
+torch = pytest.importorskip("torch")
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+import paper_2601_05031_amd as P  # noqa: E402
+from paper_2601_05031_amd import vs as V  # noqa: E402
+
+FIELD_NAMES = ["phi", "mu", "omega_x", "omega_y", "omega_z", "psi_x", "psi_y", "psi_z"]
+L = {k: i for i, k in enumerate(V.LOG_FIELDS)}
+# the direct pass solves to rounding (relative residual ~1e-14); a correction cycle moves the
+# fields by that residual times the solve's amplification (the pins of the plain and corrected
+# paths use the same bar)
+TOL = 1e-11
+
+
+def rel_l2(a, b):
+    nb = float(np.linalg.norm(b))
+    return float(np.linalg.norm(a - b)) / (nb if nb > 0 else 1.0)
+
+
+def case(shape, seed):
+    return workload("vesicle32", grid=GridSpec(*shape), R0=min(shape) / 4.0, seed=seed, rate_V=10.0, k_A=1.0,
+                    dt=5e-4, max_cycles=1)
+
+
+def missing_step(w, nsteps, lo=2):
+    """(fields, log, rtol, k): an uncorrected run whose step k is the first above rtol."""
+    s = P.solver_for(w)
+    s.step(w.dt, nsteps)
+    f, log = s.fields(), s.log()
+    s.close()
+    r = log[:, L["relres"]]
+    for k in range(lo, nsteps + 1):
+        if r[k] > r[:k].max() * (1.0 + 1e-9):
+            return f, log, 0.5 * (r[:k].max() + r[k]), k
+    return f, log, None, None
+
+
+def step_allowing_noconv(call):
+    try:
+        call()
+        return V.VS_OK
+    except V.VsError as e:
+        assert e.code == V.VS_E_NOCONV, e
+        return e.code
+
+
+# plane-size and line-size transforms, general (non two-pass) lengths, the two-lane column solve
+@pytest.mark.parametrize("shape", [(32, 21, 32), (32, 19, 64), (18, 16, 24), (16, 6, 36), (16, 5, 32)])
+def test_a_step_that_misses_is_corrected_and_the_call_finished(shape):
+    nsteps = 8
+    for seed in range(6):
+        w = case(shape, seed)
+        ref, rlog, rtol, k = missing_step(w, nsteps)
+        if k is not None and k < nsteps:
+            break
+    else:
+        pytest.skip("no run whose residual rises at a middle step")
+    print(f"case halt {shape} seed={seed} rtol={rtol:.3e} at step {k} of {nsteps}", flush=True)
+    s = P.solver_for(w.with_(max_cycles=3, rtol=rtol))
+    code = step_allowing_noconv(lambda: s.step(w.dt, nsteps))
+    got, log, sc = s.fields(), s.log(), s.scalars()
+    step_allowing_noconv(lambda: s.step(w.dt, 1))   # the state goes on working
+    assert s.scalars()["step"] == nsteps + 1
+    s.close()
+    assert sc["step"] == nsteps
+    assert list(log[:, L["index"]]) == list(range(nsteps + 1))
+    assert np.allclose(log[:, L["V"]], rlog[:, L["V"]], rtol=1e-12)
+    cyc = log[:, L["cycles"]]
+    assert list(cyc[1:k]) == [2 * (q + 1) for q in range(k - 1)]       # passed at once
+    assert cyc[k] > 2 * k                                              # took correction cycles
+    assert (np.diff(cyc[1:]) >= 2).all()
+    assert (code == V.VS_OK) == bool((log[:, L["conv"]] == 1).all())
+    errs = {q: rel_l2(got[q], ref[q]) for q in FIELD_NAMES}
+    print("  " + " ".join(f"{q}={v:.1e}" for q, v in errs.items()), f"code={code} cycles={cyc}", flush=True)
+    assert max(errs.values()) <= TOL, errs
+
+
+def test_an_instance_of_a_batch_halts_alone():
+    shape, nsteps = (32, 21, 32), 8
+    runs = []
+    for seed in range(12):
+        w = case(shape, seed)
+        ref, rlog, rtol, k = missing_step(w, nsteps)
+        runs.append((w, ref, rtol if k is not None and k < nsteps and len(runs) % 2 else 1e-10, k))
+        if len(runs) >= 4 and any(r[2] < 1e-12 for r in runs):
+            break
+    else:
+        pytest.skip("no run whose residual rises at a middle step")
+    print(f"case halt batch rtols={[r[2] for r in runs]} k={[r[3] for r in runs]}", flush=True)
+    V.set_launch_shapes(shape + (1.0,), dict(adv_slab=4, va_maxb=1024, res_maxb=1024, seg_alt=0, mu_kind=0, mu_ni=8,
+                                             plane=0))
+    solvers = [P.solver_for(w.with_(max_cycles=3, rtol=rtol)) for w, _, rtol, _ in runs]
+    b = V.Batch(solvers, nstreams=2)
+    step_allowing_noconv(lambda: b.step([w.dt for w, *_ in runs], nsteps))
+    b.close()
+    for s, (w, ref, rtol, k) in zip(solvers, runs):
+        got, log, sc = s.fields(), s.log(), s.scalars()
+        s.close()
+        assert sc["step"] == nsteps and list(log[:, L["index"]]) == list(range(nsteps + 1))
+        errs = {q: rel_l2(got[q], ref[q]) for q in FIELD_NAMES}
+        assert max(errs.values()) <= TOL, errs
+        cyc = log[:, L["cycles"]]
+        if rtol > 1e-12:
+            assert list(cyc[1:]) == [2 * (q + 1) for q in range(nsteps)]
+            for q in FIELD_NAMES:
+                assert np.array_equal(got[q], ref[q]), q
+        else:
+            assert cyc[-1] > 2 * nsteps
+
+
+def test_an_unreachable_rtol_is_reported_by_the_initial_solve():
+    with pytest.raises(V.VsError) as e:
+        P.solver_for(case((32, 21, 32), 0).with_(rtol=1e-30, max_cycles=3))
+    assert e.value.code == V.VS_E_NOCONV
+
+
+def test_reverse_step_that_misses_takes_the_general_path():
+    w = case((32, 13, 32), 3)
+    s = P.solver_for(w)
+    rng = np.random.default_rng(2)
+    a = torch.tensor(rng.standard_normal(w.grid.shape), device="cuda")
+    # rtol between the forward solve's residual (which must pass) and the adjoint's is not known:
+    # take the smallest rtol the forward run meets, so the adjoint solves may or may not miss; the
+    # gradient agrees with the plain one either way
+    rtol = s.scalars()["relres"] * 1.01
+    b0, b1 = torch.empty_like(a), torch.empty_like(a)
+    k0, s0 = s.grad_step(w.dt, a, b0)
+    t = P.solver_for(w.with_(max_cycles=4, rtol=rtol))
+    out = {}
+    code = step_allowing_noconv(lambda: out.update(d=t.grad_step(w.dt, a, b1)))
+    print(f"case reverse rtol={rtol:.2e} code={code}", flush=True)
+    e = rel_l2((b1 - a).cpu().numpy(), (b0 - a).cpu().numpy())
+    assert e <= TOL, e
+    if code == V.VS_OK:
+        assert out["d"][0] == pytest.approx(k0, rel=1e-9) and out["d"][1] == pytest.approx(s0, rel=1e-9, abs=1e-18)
+    s.close()
+    t.close()
