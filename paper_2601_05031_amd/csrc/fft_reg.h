@@ -1,6 +1,6 @@
-// In-register complex DFTs of small compile-time sizes (2, 3, 4, 6, 8, 12, 16), natural order
-// in and out, forward sign exp(-2 pi i p k / R), in FP64 (double2) or FP32 (float2). Sizes 6, 8, 12, 16 are built by one
-// Cooley-Tukey split R = R1 * R2 (input index k1 + R1 k2, output index p2 + R2 p1) with
+// In-register complex DFTs of small compile-time sizes (2, 3, 4, 6, 8, 9, 12, 16, 18), natural
+// order in and out, forward sign exp(-2 pi i p k / R), in FP64 (double2) or FP32 (float2). Sizes
+// 6, 8, 9, 12, 16, 18 are built by one Cooley-Tukey split R = R1 * R2 (input index k1 + R1 k2, output index p2 + R2 p1) with
 // compile-time twiddles exp(-2 pi i k1 p2 / R).
 #pragma once
 
@@ -57,9 +57,25 @@ __host__ __device__ constexpr cd w12(int m) {
     }
 }
 
-// exp(-2 pi i m / R) for R dividing 16 or 12.
+// exp(-2 pi i m / 18) = cos(pi m / 9) - i sin(pi m / 9)
+__host__ __device__ constexpr cd w18(int m) {
+    // cos(20 deg k), k = 0 .. 9; sin(20 deg k) by symmetry from the table of sines
+    constexpr double c[10] = {1.0, 0.93969262078590838405, 0.76604444311897803520, 0.5,
+                              0.17364817766693034885, -0.17364817766693034885, -0.5,
+                              -0.76604444311897803520, -0.93969262078590838405, -1.0};
+    constexpr double s[10] = {0.0, 0.34202014332566873304, 0.64278760968653932632,
+                              0.86602540378443864676, 0.98480775301220805937,
+                              0.98480775301220805937, 0.86602540378443864676,
+                              0.64278760968653932632, 0.34202014332566873304, 0.0};
+    m %= 18;
+    return m <= 9 ? cd{c[m], -s[m]} : cd{c[18 - m], s[18 - m]};
+}
+
+// exp(-2 pi i m / R) for R dividing 16, 12 or 18.
 __host__ __device__ constexpr cd wr(int R, int m) {
-    return (16 % R == 0) ? w16((m % R) * (16 / R)) : w12((m % R) * (12 / R));
+    return (16 % R == 0)   ? w16((m % R) * (16 / R))
+           : (12 % R == 0) ? w12((m % R) * (12 / R))
+                           : w18((m % R) * (18 / R));
 }
 
 // Complex values as HIP's double2 or float2: the transforms run in the precision of the data
@@ -185,6 +201,16 @@ template <>
 struct DFT<8> {
     template <class C>
     static __device__ __forceinline__ void run(C* x) { dft_split<2, 4>(x); }
+};
+template <>
+struct DFT<9> {
+    template <class C>
+    static __device__ __forceinline__ void run(C* x) { dft_split<3, 3>(x); }
+};
+template <>
+struct DFT<18> {
+    template <class C>
+    static __device__ __forceinline__ void run(C* x) { dft_split<2, 9>(x); }
 };
 template <>
 struct DFT<12> {

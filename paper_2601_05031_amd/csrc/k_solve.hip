@@ -1140,6 +1140,11 @@ bool fused_flow_ok(const Dims& d) {
     return seg_shape(d.M) != 0;
 }
 
+bool refined_ok(const Dims& d) {
+    auto len = [](int n) { return n == 32 || n == 48 || n == 64 || n == 96 || n == 128 || n == 192 || n == 256; };
+    return len(d.nx) && len(d.nz) && seg_shape(d.M) != 0;
+}
+
 // Residual blocks per component: slabs of x-planes chosen so that about a thousand blocks
 // cover one component (each component adds as many again).
 static SlabGrid resid_grid(const Dims& d) { return slab_grid(d.M * d.nz, d.nx, 1024); }

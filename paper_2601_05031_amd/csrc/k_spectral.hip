@@ -24,9 +24,8 @@
 // dht_x, tridiag_y, dht_x, dht_z_out, resid_norm and check for each cycle.
 // A Hartley transform of a real line is computed by a complex FFT of two lines packed as
 // (line a) + i (line b), then H_a(p) = Re A_p - Im A_p with A_p = (Z_p + conj Z_{n-p})/2,
-// and likewise for b. Line lengths n = B A (B in {8, 16}, A in {3, 4, 6, 8, 12, 16}) use a
-// two-pass register FFT; other 2^a 3^b lengths a Stockham transform in LDS with radix-4/2/3
-// passes. Twiddles come from a table exp(-2 pi i m/n).
+// and likewise for b. The lengths n = B A of two_pass_shape (most of 16 .. 256) use a two-pass
+// register FFT; other 2^a 3^b lengths a Stockham transform in LDS with radix-4/2/3 passes. Twiddles come from a table exp(-2 pi i m/n).
 #include <type_traits>
 
 #include "spectral.h"
@@ -253,8 +252,8 @@ __global__ __launch_bounds__(kBlock) void k_dht_z_out(Dims d, FftPlan pz,
 }
 
 // ---------------------------------------------------------------------------------------
-// Two-pass register transforms for line lengths n = B * A (B in {8, 16}; A in {3, 4, 6, 8,
-// 12, 16}). One 64-lane wave per block handles L = 64 / A complex lines (2L real lines):
+// Two-pass register transforms for line lengths n = B * A (two_pass_shape). A block of NT lanes
+// handles L complex lines (2L real lines); by default one wave and L = 64 / A:
 //  pass 1: item (line, k1), k1 < A: DFT_B over k2 of x[k1 + A k2] loaded from global memory,
 //          twiddle exp(-2 pi i k1 p2 / n), store Y[line][p2][k1] in LDS (padded rows);
 //  pass 2: item (line, s), s < B/2, owns the mode pair p2 = {s, B - s} ({0, B/2} for s = 0):
@@ -262,10 +261,12 @@ __global__ __launch_bounds__(kBlock) void k_dht_z_out(Dims d, FftPlan pz,
 //          sit in the same item, so both Hartley values are formed in registers and stored.
 // LM > 1: LM times the lines per block, so pass 1 takes LM rounds and pass 2 (B/2 items per
 // line) fills more lanes (A = 16 leaves half the wave idle in pass 2 with LM = 1).
-template <int B, int A, int LM = 1>
+// LX > 0: that many lines, with as many waves as pass 1 fills.
+template <int B, int A, int LM = 1, int LX = 0>
 struct TwoPass {
     static constexpr int N = B * A;
-    static constexpr int L = LM * ((64 / A) > 0 ? (64 / A) : 1);
+    static constexpr int L = LX > 0 ? LX : LM * ((64 / A) > 0 ? (64 / A) : 1);
+    static constexpr int NT = LX > 0 ? (LX * A + 63) / 64 * 64 : 64;   // block size
     static constexpr int RS = A + 1;             // padded row of Y
     static constexpr int LS = B * RS + 1;        // padded line of Y
     static constexpr int LDS = L * LS;           // double2 elements
@@ -274,17 +275,16 @@ struct TwoPass {
 // Prep: Pre prep(line) (per-line row offsets, computed once per item).
 // Loader: double2 load(pre, k1, k2) -> (line a value, line b value) at position k1 + A k2.
 // Storer: void store(pre, p, ha, hb).
-template <int B, int A, bool LINE_FAST, class T, int LM = 1, class Prep, class Load, class Store>
+template <int B, int A, bool LINE_FAST, class T, class P, class Prep, class Load, class Store>
 __device__ __forceinline__ void two_pass_hartley(C2<T>* Y, const double2* __restrict__ tw_,
                                                  Prep prep, Load load, Store store) {
     // the twiddle table is global memory (typed so, whatever the pointer's origin)
     const Gl<tw2v>* __restrict__ tw = (const Gl<tw2v>*)tw_;
-    using P = TwoPass<B, A, LM>;
     using C = C2<T>;
-    constexpr int L = P::L;
+    constexpr int L = P::L, NT = P::NT;
     const T half = (T)0.5;
 #pragma unroll 1
-    for (int it = threadIdx.x; it < L * A; it += 64) {
+    for (int it = threadIdx.x; it < L * A; it += NT) {
         const int line = LINE_FAST ? (it % L) : (it / A);
         const int k1 = LINE_FAST ? (it / L) : (it % A);
         const auto pre = prep(line);
@@ -300,7 +300,7 @@ __device__ __forceinline__ void two_pass_hartley(C2<T>* Y, const double2* __rest
     }
     __syncthreads();
 #pragma unroll 1
-    for (int it = threadIdx.x; it < L * (B / 2); it += 64) {
+    for (int it = threadIdx.x; it < L * (B / 2); it += NT) {
         const int line = LINE_FAST ? (it % L) : (it / (B / 2));
         const int s = LINE_FAST ? (it / L) : (it % (B / 2));
         const auto pre = prep(line);
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(64) void k_rhs_hz(Dims d, const double2* __restrict
             if (o.x >= 0) sc[o.x + p] = (ST)ha;
             if (o.y >= 0) sc[o.y + p] = (ST)hb;
         };
-        two_pass_hartley<B, A, false, T>(Y, tw, prepw, load, storew);
+        two_pass_hartley<B, A, false, T, P>(Y, tw, prepw, load, storew);
         return;
     }
 #pragma unroll 4
@@ -481,16 +481,22 @@ __global__ __launch_bounds__(64) void k_rhs_hz(Dims d, const double2* __restrict
     }
     __syncthreads();
     auto load = [&](const RowPair&, int, int k2) -> C { return xin[k2]; };
-    two_pass_hartley<B, A, false, T>(Y, tw, prep, load, store);
+    two_pass_hartley<B, A, false, T, P>(Y, tw, prep, load, store);
 }
 
 // dht_x, two-pass form: block = (2L consecutive z-modes q, interior row j, component c);
 // lines are the q-pairs (q, q+1), read and written as one 16-byte value.
+// L = x_lines: the 2L values of a run are whole 128-byte cache lines (16 doubles or 32 floats).
+// With one wave and 64 / A lines, n_x = 256 read 64-byte runs, so that every line was fetched by
+// two blocks on two XCDs: six components at 256^3 took 534 us against 365 us now (4.4 TB/s).
+template <int A, class ST>
+constexpr int x_lines() { return (A <= 4 ? 16 : 8) * (sizeof(ST) == 4 && A > 4 ? 2 : 1); }
 // NC: the component count of the launch (3, or 6 for the vorticity and stream-vector fields
 // together); the code is the same, the symbol tells the two launches apart in traces.
 template <int B, int A, class ST, int NC, bool BATCH>
-__global__ __launch_bounds__(64) void k_hx(Dims d, HxArgs one, const HxArgs* __restrict__ tab) {
-    using P = TwoPass<B, A>;
+__global__ __launch_bounds__((TwoPass<B, A, 1, x_lines<A, ST>()>::NT)) void k_hx(
+    Dims d, HxArgs one, const HxArgs* __restrict__ tab) {
+    using P = TwoPass<B, A, 1, x_lines<A, ST>()>;
     using T = ST;
     using C = C2<T>;
     const int inst = BATCH ? (int)blockIdx.z / NC : 0;
@@ -513,7 +519,7 @@ __global__ __launch_bounds__(64) void k_hx(Dims d, HxArgs one, const HxArgs* __r
     auto store = [&](int o, int p, T ha, T hb) {
         if (o >= 0) stc<T>(s + o + p * pstride, ha, hb);
     };
-    two_pass_hartley<B, A, true, T>(Y, a.tw, prep, load, store);
+    two_pass_hartley<B, A, true, T, P>(Y, a.tw, prep, load, store);
 }
 
 // Lines per block of the z output pass: doubled for FP32 256-long lines (see TwoPass).
@@ -580,7 +586,7 @@ __global__ __launch_bounds__(64) void k_hz_out(Dims d, ZArgs one, const ZArgs* _
                 if (rp.b >= 0) put(rp.b + p, (double)hb);
             }
         };
-        two_pass_hartley<B, A, false, T, LM>(Y, a.tw, prep, load, store);
+        two_pass_hartley<B, A, false, T, P>(Y, a.tw, prep, load, store);
     };
     if constexpr (std::is_same_v<ST, float> && NC == 6) {   // the refined mode's passes
         if (a.self) run(std::integral_constant<int, 5>{});
@@ -1011,6 +1017,7 @@ void rhs_dht_z_t(hipStream_t s, const Dims& d, const FftPlan& pz, const double2*
         return;                                                                                \
     }
     VS_TWO_PASS_CASES(VS_CASE)
+    if constexpr (sizeof(ST) == 8) { VS_TWO_PASS_CASES64(VS_CASE) }
 #undef VS_CASE
     const int rpb = z_rows_per_block(d);
     launch_kernel(k_rhs_dht_z<ST>, dim3((nrows + rpb - 1) / rpb, ncomp), dim3(kBlock), 0, s,
@@ -1024,20 +1031,22 @@ void dht_x_t(hipStream_t s, const Dims& d, const FftPlan& px, const Over<HxArgs>
     const unsigned ni = a.tab ? (unsigned)a.n : 1u;
 #define VS_CASE(b, a_)                                                                         \
     if (B == b && A == a_) {                                                                   \
-        const int qs = 2 * TwoPass<b, a_>::L;                                                  \
-        const dim3 g((d.nz + qs - 1) / qs, d.M, ncomp * ni);                                   \
+        using PX = TwoPass<b, a_, 1, x_lines<a_, ST>()>;                                       \
+        const int qs = 2 * PX::L;                                                              \
+        const dim3 g((d.nz + qs - 1) / qs, d.M, ncomp * ni), t(PX::NT);                        \
         if (ncomp > 3) {                                                                       \
-            if (a.tab) launch_kernel((k_hx<b, a_, ST, 6, true>), g, dim3(64), 0, s, d, a.one, a.tab); \
-            else launch_kernel((k_hx<b, a_, ST, 6, false>), g, dim3(64), 0, s, d, a.one, a.tab); \
+            if (a.tab) launch_kernel((k_hx<b, a_, ST, 6, true>), g, t, 0, s, d, a.one, a.tab); \
+            else launch_kernel((k_hx<b, a_, ST, 6, false>), g, t, 0, s, d, a.one, a.tab);      \
         } else if (a.tab) {                                                                    \
             if constexpr (sizeof(ST) == 8)                                                     \
-                launch_kernel((k_hx<b, a_, ST, 3, true>), g, dim3(64), 0, s, d, a.one, a.tab); \
+                launch_kernel((k_hx<b, a_, ST, 3, true>), g, t, 0, s, d, a.one, a.tab);        \
         } else {                                                                               \
-            launch_kernel((k_hx<b, a_, ST, 3, false>), g, dim3(64), 0, s, d, a.one, a.tab);    \
+            launch_kernel((k_hx<b, a_, ST, 3, false>), g, t, 0, s, d, a.one, a.tab);           \
         }                                                                                      \
         return;                                                                                \
     }
     VS_TWO_PASS_CASES(VS_CASE)
+    if constexpr (sizeof(ST) == 8) { VS_TWO_PASS_CASES64(VS_CASE) }
 #undef VS_CASE
     // general lengths: LDS Stockham transform, one instance, up to three components a launch
     const int kb = x_modes_per_block(d);
@@ -1072,6 +1081,7 @@ void dht_z_out_t(hipStream_t s, const Dims& d, const FftPlan& pz, const Over<ZAr
         return;                                                                                \
     }
     VS_TWO_PASS_CASES(VS_CASE)
+    if constexpr (sizeof(ST) == 8) { VS_TWO_PASS_CASES64(VS_CASE) }
 #undef VS_CASE
     const int rpb = z_rows_per_block(d);
     for (int c0 = 0; c0 < ncomp; c0 += 3) {
@@ -1118,10 +1128,7 @@ int plane_blocks() {
 }
 
 bool plane_fits(const Dims& d) {
-    int bx, ax, bz, az;
-    two_pass_shape(d.nx, bx, ax);
-    two_pass_shape(d.nz, bz, az);
-    return d.nx == d.nz && bx > 0 && bz > 0 && d.nx <= 128 && d.nx >= 32;
+    return d.nx == d.nz && (d.nx == 32 || d.nx == 48 || d.nx == 64 || d.nx == 96 || d.nx == 128);
 }
 
 bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,
@@ -1166,11 +1173,7 @@ bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Ov
 // The refined mode's FP32 plane forms: square planes of n_x = n_z in {32, 48, 64, 96, 128}
 // and the 128 x 256 plane (132 KB of floats).
 bool plane32_fits(const Dims& d) {
-    int bx, ax, bz, az;
-    two_pass_shape(d.nx, bx, ax);
-    two_pass_shape(d.nz, bz, az);
-    if (!bx || !bz) return false;
-    return (d.nx == d.nz && d.nx >= 32 && d.nx <= 128) || (d.nx == 128 && d.nz == 256);
+    return plane_fits(d) || (d.nx == 128 && d.nz == 256);
 }
 
 bool launch_plane32(hipStream_t s, const Dims& d, bool zfirst, const Over<ZArgs>& z,

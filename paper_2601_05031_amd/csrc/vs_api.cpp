@@ -436,10 +436,6 @@ struct StepArgs {
     X(rf[1]) X(zs[0]) X(zs[1]) X(hxc[0]) X(hxc[1]) X(trc[0]) X(trc[1]) X(zadd[0]) X(zadd[1]) \
     X(resc[0]) X(resc[1]) X(chkc[0]) X(chkc[1])
 
-// The fused refined-mode cycle and the fused FP64 pass need two-pass transform lengths and a
-// segmented tridiagonal layout; the refined mode is offered only there.
-bool refined_fused(const vs_state* S) { return S->f32 && fused_flow_ok(S->d); }
-
 // Whether the FP64 flow pass keeps its modes in the omega and psi fields themselves (every pass
 // in place on the interior rows; the wall rows stay) instead of the two spectral buffers, for
 // `nodes` nodes stepped together. A step then touches 12 fields instead of 18, so more of each
@@ -967,7 +963,7 @@ vs_status vs_init(const vs_grid* grid, const vs_walls* walls, const vs_params* p
     const Layout L = make_layout(*grid, params->rho > 0.0, params->precision == VS_FP32_REFINED);
     {
         Dims dd{grid->nx, grid->ny, grid->nz, grid->ny - 2, grid->h, 0.0, 0.0};
-        if (params->precision == VS_FP32_REFINED && !fused_flow_ok(dd))
+        if (params->precision == VS_FP32_REFINED && !refined_ok(dd))
             return fail(VS_E_UNSUPPORTED,
                         "VS_FP32_REFINED needs nx, nz in {32, 48, 64, 96, 128, 192, 256} and "
                         "4 <= ny - 2 <= 256 (the fused transform and tridiagonal forms)");

@@ -325,6 +325,8 @@ bool plane32_fits(const Dims& d);
 bool launch_plane32(hipStream_t s, const Dims& d, bool zfirst, const Over<ZArgs>& z,
                     const Over<HxArgs>& x);
 bool fused_flow_ok(const Dims& d);
+// The grids VS_FP32_REFINED accepts: nx, nz in {32, 48, 64, 96, 128, 192, 256} and 4 <= M <= 256.
+bool refined_ok(const Dims& d);
 // Both transform directions in one pass per (interior row, component), the (x, z) plane in
 // LDS: zfirst, z then x from z.spec into x.spec (the source's forward transform); otherwise x
 // then z from x.spec into z.u (the inverse of the omega and psi modes). FP64 spectral data,
