@@ -297,13 +297,15 @@ int32_t vs_profile_count(void);
 const char* vs_profile_name(int32_t kernel);
 vs_status vs_profile_read(vs_state* state, int32_t kernel, double* total_ms, int64_t* launches);
 
-/* Launch-shape autotuner. Times, on the state's own data, the candidate launch shapes of its
- * grid: the x-slab length of the phi update (2, 4, 8 planes per lane), the block caps of the
+/* Launch-shape autotuner. A grid starts with launch shapes that a rule on its sizes picks.
+ * vs_autotune times, on the state's own data, the candidate launch shapes of its grid: the x-slab
+ * length of the phi update (2, 4, 8 planes per lane), the block caps of the
  * volume/area partials (256 .. 2048) and of the flow residual (512 .. 4096), the form of the
- * chemical potential (LDS tiles, or for nz in {64, 128, 256} register marching with 1 or 2
- * rows per wave and 2 .. 16 planes per slab; all forms give the same bits) and, for
+ * chemical potential (LDS tiles, or for nz <= 128, or nz <= 256 and a multiple of 4, register
+ * marching with 1 or 2 rows per lane group and 2 .. 16 planes per slab; all forms give the same
+ * bits) and, for
  * ny - 2 in {30, 46, 62, 94, 126, 254}, the segment layout of the tridiagonal solves (the
- * default or one with twice/half the lanes per mode) and, in FP64 with nx = nz in
+ * default or one with twice/half the lanes per mode) and, in FP64 with nx and nz in
  * {32, 48, 64, 96, 128}, whether the x and z transforms of a direction run as one pass over
  * each (x, z) plane held in LDS (plane = 1) or as two line passes (0), one coordinate at a
  * time, and keeps the fastest for every state of that grid in this process. The state's fields
@@ -312,8 +314,9 @@ vs_status vs_profile_read(vs_state* state, int32_t kernel, double* total_ms, int
 vs_status vs_autotune(vs_state* state, int32_t picked[7]);
 /* Set the launch shapes of a grid by hand (the seven values vs_autotune reports, e.g. from an
  * earlier tuning run), for every state of that grid in this process from the next launch on.
- * Shapes that the grid cannot use fall back to the default form (the register-marching
- * chemical potential needs nz in {64, 128, 256}; seg_alt needs ny - 2 in the list above).
+ * Shapes that the grid cannot use fall back to the other form (the register-marching
+ * chemical potential to the tiles, the plane pass to line passes; seg_alt needs ny - 2 in the
+ * list above).
  * Checks ranges only; results are unchanged except in the order of the partial sums and, with
  * plane = 1, in the rounding of the z transforms (their rows are paired differently). */
 vs_status vs_set_launch_shapes(const vs_grid* grid, const int32_t shapes[7]);

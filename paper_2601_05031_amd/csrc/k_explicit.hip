@@ -531,10 +531,10 @@ __global__ __launch_bounds__(kBlock) void k_mu_tile(Dims d, int va_nb, MuArgs on
     }
 }
 
-// mu by register marching, for n_z = 64 ZPL (ZPL in {1, 2, 4}): one wave covers whole z rows,
-// ZPL consecutive z per lane, so the periodic z neighbours come from the lane's own values and,
-// at its ends, from the previous and next lane (a rotation across the whole wave). A wave owns
-// RJ consecutive rows and walks ni consecutive x-planes; the phi planes i .. i+3 of the rows
+// mu by register marching: W = n_z / ZPL <= 64 lanes cover a whole z row, ZPL consecutive z per
+// lane, so the periodic z neighbours come from the lane's own values and, at its ends, from the
+// previous and next lane (a rotation across the row's W lanes). A wave holds 64 / W such groups
+// (the lanes left over idle); a group owns RJ consecutive rows and walks ni consecutive x-planes; the phi planes i .. i+3 of the rows
 // j0-2 .. j0+RJ+1 (mirror rows past the walls, so g there is the mirror ghost of g) and g of the
 // planes i-1 .. i+1 stay in registers, and L_h phi of a plane is kept from the g computation
 // of that plane. The phi plane three ahead is loaded first in each step, so it is in flight
@@ -546,7 +546,9 @@ __global__ __launch_bounds__(kBlock) void k_mu_reg(Dims d, int va_nb, int ni, Mu
                                                   const MuArgs* __restrict__ tab) {
     constexpr int NR = RJ + 4;                    // phi rows j0-2 .. j0+RJ+1
     __shared__ double shv[2 * 16];
-    const int ngr = (d.ny + 4 * RJ - 1) / (4 * RJ);   // groups of four waves' rows
+    const int W = d.nz / ZPL, ng = 64 / W;            // lanes per row, row groups per wave
+    const int rpb = 4 * ng * RJ;                      // rows per block
+    const int ngr = (d.ny + rpb - 1) / rpb;
     const int nsl = (d.nx + ni - 1) / ni;
     int inst;
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), ngr * nsl, inst);
@@ -556,12 +558,14 @@ __global__ __launch_bounds__(kBlock) void k_mu_reg(Dims d, int va_nb, int ni, Mu
     MT* __restrict__ mu = (MT*)va.mu;   // stored through a buffer resource
     const int sl = lb / ngr, gr = lb - sl * ngr;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j0 = (gr * 4 + wv) * RJ;
+    const int grp = lane / W, li = lane - grp * W;
+    const bool live = grp < ng;                       // the others work on row 0 and store nothing
+    const int j0 = live ? ((gr * 4 + wv) * ng + grp) * RJ : 0;
     const int i0 = sl * ni, i1 = min(d.nx, i0 + ni);
     const int plane = d.ny * d.nz;
-    const int zo = lane * ZPL;
+    const int zo = li * ZPL;
     const double eps2 = va.eps * va.eps, C_b = va.C_b, sigma = va.sigma;
-    const int lprev = (lane + 63) & 63, lnext = (lane + 1) & 63;
+    const int lprev = li == 0 ? lane + W - 1 : lane - 1, lnext = li == W - 1 ? lane - li : lane + 1;
     int roff[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) roff[r] = mirror_row(j0 - 2 + r, d.ny) * d.nz + zo;
@@ -640,7 +644,7 @@ __global__ __launch_bounds__(kBlock) void k_mu_reg(Dims d, int va_nb, int ni, Mu
 #pragma unroll
         for (int r = 0; r < RJ; ++r) {
             const int j = j0 + r;
-            const bool keep = j < d.ny;
+            const bool keep = live && j < d.ny;
 #pragma unroll
             for (int q = 0; q < ZPL; ++q) {
                 const double p = A[r + 2][q];
@@ -1017,20 +1021,32 @@ void launch_va_partials(hipStream_t s, const Dims& d, const Over<VaArgs>& a) {
     else go(k_va_partials<true>, k_va_partials<false>);
 }
 
-// The chemical potential runs as x-marching LDS tiles (k_mu_tile, any grid) or, for n_z in
-// {64, 128, 256}, by register marching (k_mu_reg) with RJ rows per wave and mu_ni planes per
-// slab; the autotuner picks (mu_kind: 0 tiles, 1 or 2 register marching with RJ = 1 or 2).
+// z values per lane of the register-marching chemical potential: a row in at most 64 lanes; 0: none
+// fits (n_z above 256, or above 128 and no multiple of 4).
+int mu_reg_zpl(const Dims& d) {
+    if (d.nz <= 64) return 1;
+    if (d.nz <= 128) return 2;
+    return d.nz <= 256 && d.nz % 4 == 0 ? 4 : 0;
+}
+// Blocks of that form with RJ rows per group and ni planes per slab.
+int mu_reg_blocks(const Dims& d, int RJ, int ni) {
+    const int rpb = 4 * (64 / (d.nz / mu_reg_zpl(d))) * RJ;
+    return ((d.ny + rpb - 1) / rpb) * ((d.nx + ni - 1) / ni);
+}
+
+// The chemical potential runs by register marching (k_mu_reg) with mu_kind = 1 or 2 rows per
+// lane group and mu_ni planes per slab, or as x-marching LDS tiles (k_mu_tile, mu_kind = 0 or no
+// register form).
 template <bool BEND, class MT>
 static void mu_t(hipStream_t s, const Dims& d, const Over<MuArgs>& a) {
     const unsigned ni_ = a.tab ? (unsigned)a.n : 1u;
     const int vnb = va_partial_blocks(d);
     const Tuning tu = tuning_for(d);
-    const int zpl = d.nz / 64;
-    if (tu.mu_kind > 0 && d.nz % 64 == 0 && (zpl == 1 || zpl == 2 || zpl == 4)) {
+    const int zpl = mu_reg_zpl(d);
+    if (tu.mu_kind > 0 && zpl > 0) {
         const int RJ = tu.mu_kind;
         const int ni = tu.mu_ni > 0 ? tu.mu_ni : 8;
-        const int nb = ((d.ny + 4 * RJ - 1) / (4 * RJ)) * ((d.nx + ni - 1) / ni);
-        const dim3 gr(nb * ni_);
+        const dim3 gr(mu_reg_blocks(d, RJ, ni) * ni_);
         auto go = [&](auto kt, auto kf) {
             if (a.tab) launch_kernel(kt, gr, dim3(kBlock), 0, s, d, vnb, ni, a.one, a.tab);
             else launch_kernel(kf, gr, dim3(kBlock), 0, s, d, vnb, ni, a.one, a.tab);

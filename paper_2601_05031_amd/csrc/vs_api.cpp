@@ -298,7 +298,29 @@ struct TuneEntry {
 };
 std::mutex g_tune_mu;
 std::vector<TuneEntry> g_tune;
-constexpr Tuning kDefaultTuning{4, 1024, 1024, 0, 0, 8, 0};
+// The shapes of a grid that was not tuned, from sweeps of 12 grids of 32^3 .. 256^3:
+//  adv_slab  the longest of 8, 4, 2 planes that leaves at least 800 blocks (three per CU):
+//            64^3 9.2 us at 2 planes against 10.0 at 4; 96^3 11.9 at 2 against 12.7; 128^3 19.8 at
+//            4 against 20.5 at 2; 256^3 195 at 8 against 200 at 4;
+//  mu        register marching wherever a row fits a wave, two rows per group and the longest slab
+//            of 16, 8, 4, 2 planes that fills the CUs at once (two blocks per CU, one at four z
+//            per lane): 64^3 6.7 us at 2 planes (LDS tiles 10.1), 128^3 11.1 at 4 (16.6),
+//            128 x 128 x 256 20.7 at 8 (31.0), 256^3 63 at 16 (104);
+//  plane     both transforms of a direction in one pass wherever the plane fits in LDS (k_plane.hip).
+// The partials' block caps and the tridiagonal layout are best or within 3% at their defaults.
+Tuning default_tuning(const Dims& d) {
+    Tuning t{2, 1024, 1024, 0, 0, 8, plane_fits(d) ? 1 : 0};
+    const int gx = (d.ny * (d.nz % 32 == 0 ? d.nz / 2 : d.nz) + 255) / 256;
+    for (int s : {4, 8})
+        if (gx * ((d.nx + s - 1) / s) >= 800) t.adv_slab = s;
+    if (const int zpl = mu_reg_zpl(d)) {
+        t.mu_kind = 2;
+        t.mu_ni = 2;
+        for (int n : {4, 8, 16})
+            if (mu_reg_blocks(d, 2, n) >= (zpl == 4 ? 256 : 512)) t.mu_ni = n;
+    }
+    return t;
+}
 
 void set_tuning(const Dims& d, const Tuning& t, bool fp64 = false) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -324,7 +346,7 @@ Tuning vs::tuning_for(const Dims& d) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto& e : g_tune)
         if (e.k == TuneKey{d.nx, d.ny, d.nz}) return e.t;
-    return kDefaultTuning;
+    return default_tuning(d);
 }
 
 namespace {
@@ -707,7 +729,7 @@ bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_
     }
     // The direct transform reads S alone: the omega wall terms go into mode (0, 0) of the
     // tridiagonal solve.
-    // With the plane form (tuned, n_x = n_z up to 128) each direction is one pass.
+    // With the plane form (n_x and n_z up to 128) each direction is one pass.
     const bool plane = tuning_for(c.d).plane && plane_fits(c.d);
     if (plane) {
         timed_cfg(c, K_DHT_ZX, [&] { launch_plane(c.st, c.d, true, 3, A.zfwd, A.hx3); });
@@ -1711,11 +1733,10 @@ vs_status autotune_state(vs_state* S, Tuning* picked) {
         launch_va_partials(c.st, c.d, A.va);
         launch_mu(c.st, c.d, c.model, pr, A.mu);
     });
-    // the chemical potential's form: LDS tiles, or register marching (n_z in {64, 128, 256})
-    // with 1 or 2 rows per wave and 2 .. 16 planes per slab, as one coordinate
+    // the chemical potential's form: LDS tiles, or register marching (where a row fits a wave)
+    // with 1 or 2 rows per lane group and 2 .. 16 planes per slab, as one coordinate
     {
-        const int zpl = S->d.nz / 64;
-        const bool reg_ok = S->d.nz % 64 == 0 && (zpl == 1 || zpl == 2 || zpl == 4);
+        const bool reg_ok = mu_reg_zpl(S->d) > 0;
         const int cand[][2] = {{0, 8}, {1, 2}, {1, 4}, {1, 8}, {1, 16}, {2, 2}, {2, 4}, {2, 8}, {2, 16}};
         int bk = t.mu_kind, bn = t.mu_ni;
         float tb = 1e30f;

@@ -138,8 +138,8 @@ static inline SlabGrid slab_grid(int plane, int nx, int maxb) {
 constexpr int kPartialSlots = 17;     // values per block; stored value-major: part[q * kMaxPartialBlocks + b]
 
 // ---------------------------------------------------------------- tuned launch shapes
-// Launch shapes that the autotuner (vs_autotune) picks per grid by timing the kernels on a
-// state's own data; every launcher reads them at launch time. Defaults until a grid is tuned.
+// Launch shapes of a grid: those of a rule on its sizes (default_tuning), until the autotuner
+// (vs_autotune) times the kernels on a state's own data. Every launcher reads them at launch time.
 struct Tuning {
     int adv_slab;   // x-planes each lane of the phi update walks (2, 4 or 8)
     int va_maxb;    // block cap of the volume/area partials (sets their x-slab length)
@@ -150,6 +150,8 @@ struct Tuning {
     int plane;      // 1: both transform directions of the FP64 flow pass in one plane pass
 };
 Tuning tuning_for(const Dims& d);
+int mu_reg_zpl(const Dims& d);                          // z per lane of the register form, 0: none
+int mu_reg_blocks(const Dims& d, int RJ, int ni);       // its blocks
 bool seg_has_alt(int M);   // the pair solves of M interior rows have a second layout
 
 // ---------------------------------------------------------------- launches over instances
@@ -330,7 +332,7 @@ bool refined_ok(const Dims& d);
 // Both transform directions in one pass per (interior row, component), the (x, z) plane in
 // LDS: zfirst, z then x from z.spec into x.spec (the source's forward transform); otherwise x
 // then z from x.spec into z.u (the inverse of the omega and psi modes). FP64 spectral data,
-// n_x = n_z in {32, 48, 64, 96, 128}, no accumulation, gated per instance by z.gate; returns
+// n_x and n_z in {32, 48, 64, 96, 128}, no accumulation, gated per instance by z.gate; returns
 // false (nothing launched) otherwise.
 bool plane_fits(const Dims& d);
 bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,

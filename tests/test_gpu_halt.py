@@ -89,6 +89,9 @@ def test_a_step_that_misses_is_corrected_and_the_call_finished(shape):
 
 def test_an_instance_of_a_batch_halts_alone():
     shape, nsteps = (32, 21, 32), 8
+    # the same launch shapes for the single runs and the batch (which tunes grids it has not seen)
+    V.set_launch_shapes(shape + (1.0,), dict(adv_slab=4, va_maxb=1024, res_maxb=1024, seg_alt=0, mu_kind=0, mu_ni=8,
+                                             plane=0))
     runs = []
     for seed in range(12):
         w = case(shape, seed)
@@ -99,8 +102,6 @@ def test_an_instance_of_a_batch_halts_alone():
     else:
         pytest.skip("no run whose residual rises at a middle step")
     print(f"case halt batch rtols={[r[2] for r in runs]} k={[r[3] for r in runs]}", flush=True)
-    V.set_launch_shapes(shape + (1.0,), dict(adv_slab=4, va_maxb=1024, res_maxb=1024, seg_alt=0, mu_kind=0, mu_ni=8,
-                                             plane=0))
     solvers = [P.solver_for(w.with_(max_cycles=3, rtol=rtol)) for w, _, rtol, _ in runs]
     b = V.Batch(solvers, nstreams=2)
     step_allowing_noconv(lambda: b.step([w.dt for w, *_ in runs], nsteps))
