@@ -15,6 +15,33 @@ __device__ __forceinline__ double fc_wave_sum(double v) {
     return v;
 }
 
+// Clears the status words and residual scalars at the start of a call (one thread).
+__device__ __forceinline__ void clear_status(double* scal, int* istat) {
+    scal[SC_RELRES_MAX] = 0.0;
+    scal[SC_RELRES_LAST] = 0.0;
+    istat[IS_FLAGS] = 0;
+    istat[IS_CYCLES] = 0;
+    istat[IS_CONV] = 0;
+    istat[IS_HALT] = 0;
+    istat[IS_PASSED] = 0;
+}
+
+// Writes the scalars and status words to the host copy, so that the call that waits for the stream
+// needs no transfer. Every thread of one block (at least 64) calls it, after a barrier behind the
+// last change. The stores are system-scope atomics to fine-grained memory, complete when the kernel
+// is: a system fence here would write every dirty L2 line back first.
+__device__ __forceinline__ void status_to_host(const double* scal, const int* istat, char* host) {
+    const int t = threadIdx.x;
+    if (t < SC_NSCAL) {
+        __hip_atomic_store(reinterpret_cast<double*>(host) + t, *(const volatile double*)(scal + t),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else if (t < SC_NSCAL + IS_NSTAT) {
+        const int q = t - SC_NSCAL;
+        __hip_atomic_store(reinterpret_cast<int*>(host + kHostStatIst) + q, *(const volatile int*)(istat + q),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Call from every thread of one block (a multiple of 64 threads, at most 1024); sh holds
 // 4 * 16 doubles. mode: a CheckMode. CK_GATED (a defect-correction cycle that may be followed
 // by another): the convergence flag gates the next cycle and the miss is not yet an error.

@@ -99,15 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_advect(
     double* __restrict__ partials, AdjZero zw, double* scal, int* istat) {
     extern __shared__ double lds[];
     __shared__ double sh[3 * 16];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scal[SC_RELRES_MAX] = 0.0;
-        scal[SC_RELRES_LAST] = 0.0;
-        istat[IS_FLAGS] = 0;
-        istat[IS_CYCLES] = 0;
-        istat[IS_CONV] = 0;
-        istat[IS_HALT] = 0;
-        istat[IS_PASSED] = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) clear_status(scal, istat);
     const int nz = d.nz;
     const size_t plane = (size_t)d.ny * nz;
     const double r2h = d.inv_2h;
@@ -532,7 +524,9 @@ struct AdjSums {
     const double* part;
     int nb_src, nb_mu1;
     int psi_on;       // the psi-wall coupling came from k_adj_source (else it is in scal already)
-    double* scal;     // block 0 writes SC_ADJ_PSIC, SC_ADJ_OMC, SC_ADJ_KAPPA, SC_ADJ_GAMMA
+    double* scal;     // block 0 writes SC_ADJ_PSIC, SC_ADJ_OMC, SC_ADJ_KAPPA, SC_ADJ_GAMMA and
+    const int* istat; // then the host copy of the status
+    char* host;
 };
 __global__ __launch_bounds__(kBlock) void k_adj_mu2(const double* __restrict__ phi,
                                                    const double* __restrict__ mubar,
@@ -566,6 +560,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_mu2(const double* __restrict__ p
         sums.scal[SC_ADJ_KAPPA] = v[1];
         if (sums.psi_on) sums.scal[SC_ADJ_PSIC] = v[2];
         sums.scal[SC_ADJ_OMC] = v[3];
+    }
+    if (b0) {
+        __syncthreads();
+        status_to_host(sums.scal, sums.istat, sums.host);
     }
     const SlabIter it = slab_iter(d, sg);
     if (!it.ok) return;
@@ -701,11 +699,11 @@ void launch_adj_mu2(hipStream_t s, const Dims& d, const double* phi, const doubl
                     const double* gbar, const double* scal, int model, double C_b, double eps,
                     double sigma, double dt, double mobility, double rate_V, double k_A,
                     double* phibar, double* part, bool mu1_ran, bool psi_from_source,
-                    double* scal_out) {
+                    double* scal_out, const int* istat, char* host) {
     const AdjTile tl = adj_tile(d);
     const SlabGrid g1 = adj_slab_grid(d);
     const AdjSums sums{part, tl.ntile * tl.nslab, mu1_ran ? g1.gx * g1.gi : 0, psi_from_source ? 1 : 0,
-                       scal_out};
+                       scal_out, istat, host};
     const SlabGrid g = adj_slab_grid(d);
     launch_kernel(k_adj_mu2, dim3(g.gx * g.gi), dim3(kBlock), 0, s, phi, mubar, gbar, scal, d, model,
                   C_b, eps, sigma, dt, mobility, rate_V, k_A, g, phibar, sums);

@@ -12,6 +12,7 @@
 //     are linear in the wall data and the no-body fields (polynomials of degree <= 3 in y)
 //     solve them exactly, so a change of wall speeds adds the difference of the no-body fields
 //     to omega_x and psi_x.
+#include "flow_check.h"
 #include "stencil.h"
 
 namespace vs {
@@ -123,7 +124,8 @@ __global__ __launch_bounds__(kBlock) void k_diag(const double* __restrict__ phi,
 }
 
 __global__ __launch_bounds__(1024) void k_diag_finalize(const double* __restrict__ partials,
-                                                       int nblocks, double* scal) {
+                                                       int nblocks, double* scal, const int* istat,
+                                                       char* host) {
     __shared__ double sh[4 * 16];
     __shared__ double shm[2 * 16];
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -159,6 +161,8 @@ __global__ __launch_bounds__(1024) void k_diag_finalize(const double* __restrict
         scal[SC_DG_SMAX] = mm;
         scal[SC_DG_VMAX] = mmv;
     }
+    __syncthreads();
+    status_to_host(scal, istat, host);
 }
 
 __global__ __launch_bounds__(kBlock) void k_shift_profiles(double* __restrict__ om,
@@ -178,7 +182,8 @@ __global__ __launch_bounds__(kBlock) void k_shift_profiles(double* __restrict__ 
 void launch_diagnostics(hipStream_t s, const Dims& d, const double* phi, double* const omega[3],
                         double* const psi[3], const double* prof, double vz_lo, double vz_hi,
                         double eta, int model, double eps, double sigma, double* sigma_t,
-                        double* part, double* scal, double* const vscratch[3]) {
+                        double* part, double* scal, double* const vscratch[3], const int* istat,
+                        char* host) {
     const SlabGrid g = slab_grid(d.ny * d.nz, d.nx, kMaxPartialBlocks);
     const Vel vel{psi[0], psi[1], psi[2], vz_lo, vz_hi};
     const int nb = g.gx * g.gi;
@@ -188,7 +193,7 @@ void launch_diagnostics(hipStream_t s, const Dims& d, const double* phi, double*
                   (const double*)omega[1], (const double*)omega[2], vel,
                   (const double*)vscratch[0], (const double*)vscratch[1],
                   (const double*)vscratch[2], prof, d, eta, model, eps, sigma, g, sigma_t, part);
-    launch_kernel(k_diag_finalize, dim3(1), dim3(1024), 0, s, (const double*)part, nb, scal);
+    launch_kernel(k_diag_finalize, dim3(1), dim3(1024), 0, s, (const double*)part, nb, scal, istat, host);
 }
 
 void launch_shift_profiles(hipStream_t s, const Dims& d, double* omega_x, double* psi_x,

@@ -96,6 +96,7 @@ __global__ __launch_bounds__(kBlock) void k_advance_x(Dims d, SlabGrid sg, AdvAr
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const AdvArgs a = inst_args<BATCH>(one, tab, inst);
     if (halted(a.gate)) return;
+    if (a.reset && lb == 0 && threadIdx.x == 0) clear_status(a.scal, a.reset);
     if (a.ck_part && lb == 0) {
         // the previous step's flow check, off the critical path of this kernel's other blocks
         __shared__ double shc[4 * 16];
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_advance_x2(Dims d, SlabGrid sg, AdvA
     const int lb = split_block<BATCH>(xcd_block(blockIdx.x, gridDim.x), nb, inst);
     const AdvArgs a = inst_args<BATCH>(one, tab, inst);
     if (halted(a.gate)) return;
+    if (a.reset && lb == 0 && threadIdx.x == 0) clear_status(a.scal, a.reset);
     if (a.ck_part && lb == 0) {
         __shared__ double shc[4 * 16];
         flow_check_block(a.ck_part, a.ck_nb, a.ck_rtol, a.scal, a.ck_istat, shc, a.ck_mode, a.ck_log);
@@ -942,16 +944,9 @@ __global__ __launch_bounds__(kBlock) void k_zero_walls(Fields6 f, Dims d) {
     f.p[blockIdx.y][node(d, i, j, k)] = 0.0;
 }
 
-__global__ void k_reset_stats(double* scal, int* istat) {
-    if (threadIdx.x == 0) {
-        scal[SC_RELRES_MAX] = 0.0;
-        scal[SC_RELRES_LAST] = 0.0;
-        istat[IS_FLAGS] = 0;
-        istat[IS_CYCLES] = 0;
-        istat[IS_CONV] = 0;
-        istat[IS_HALT] = 0;
-        istat[IS_PASSED] = 0;
-    }
+__global__ __launch_bounds__(64) void k_reset_stats(const StatPtrs* __restrict__ tab, int n) {
+    const int t = blockIdx.x * 64 + threadIdx.x;
+    if (t < n) clear_status(tab[t].scal, tab[t].istat);
 }
 
 
@@ -1113,8 +1108,8 @@ void launch_source(hipStream_t s, const Dims& d, Prec pr, const Over<SrcArgs>& a
         source_t<double>(s, d, a);
 }
 
-void launch_reset_stats(hipStream_t s, double* scal, int* istat) {
-    launch_kernel(k_reset_stats, dim3(1), dim3(64), 0, s, scal, istat);
+void launch_reset_stats(hipStream_t s, const StatPtrs* tab, int n) {
+    launch_kernel(k_reset_stats, dim3((n + 63) / 64), dim3(64), 0, s, tab, n);
 }
 
 }  // namespace vs

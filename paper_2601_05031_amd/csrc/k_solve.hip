@@ -903,32 +903,10 @@ __global__ __launch_bounds__(kBlock) void k_rhs_pred(Dims d, SlabGrid sg, RhsFlo
     else walk(std::integral_constant<int, 2>{});
 }
 
-// check: relative residual sqrt(sum_c r^2 / sum_c b~^2) in a fixed summation order; sets the
-// convergence flag that gates the following cycles, counts the cycle and raises ST_NOCONV
-// on the last allowed cycle, ST_NONFINITE on NaN/Inf.
-__global__ __launch_bounds__(1024) void k_check(const double* __restrict__ partials,
-                                               int nblocks, double rtol, int last_cycle,
-                                               double* scal, int* istat, const int* gate,
-                                               int slot0, int role, double* log) {
-    if (gate && *gate) return;
-    __shared__ double sh[2 * 16];
+// The final decision of k_check, from the wave sums of r^2 (sh) and b~^2 (sh + 16).
+__device__ __forceinline__ void check_one(const double* sh, int nw, double rtol, int last_cycle,
+                                          double* scal, int* istat, int role, double* log) {
     double rr = 0.0, bb = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-        const double* pb = partials + (size_t)slot0 * kMaxPartialBlocks + b;
-        rr += pb[0 * kMaxPartialBlocks] + pb[1 * kMaxPartialBlocks] + pb[2 * kMaxPartialBlocks];
-        bb += pb[3 * kMaxPartialBlocks] + pb[4 * kMaxPartialBlocks] + pb[5 * kMaxPartialBlocks];
-    }
-    rr = wave_sum(rr);
-    bb = wave_sum(bb);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (lane == 0) {
-        sh[w] = rr;
-        sh[16 + w] = bb;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    rr = 0.0;
-    bb = 0.0;
     for (int i = 0; i < nw; ++i) {
         rr += sh[i];
         bb += sh[16 + i];
@@ -966,15 +944,45 @@ __global__ __launch_bounds__(1024) void k_check(const double* __restrict__ parti
     if (!isfinite(rr) || !isfinite(bb)) istat[IS_FLAGS] |= ST_NONFINITE;
 }
 
+// check: relative residual sqrt(sum_c r^2 / sum_c b~^2) in a fixed summation order; sets the
+// convergence flag that gates the following cycles, counts the cycle and raises ST_NOCONV
+// on the last allowed cycle, ST_NONFINITE on NaN/Inf.
+__global__ __launch_bounds__(1024) void k_check(const double* __restrict__ partials,
+                                               int nblocks, double rtol, int last_cycle,
+                                               double* scal, int* istat, const int* gate,
+                                               int slot0, int role, double* log, char* host) {
+    if (gate && *gate) return;
+    __shared__ double sh[2 * 16];
+    double rr = 0.0, bb = 0.0;
+    for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
+        const double* pb = partials + (size_t)slot0 * kMaxPartialBlocks + b;
+        rr += pb[0 * kMaxPartialBlocks] + pb[1 * kMaxPartialBlocks] + pb[2 * kMaxPartialBlocks];
+        bb += pb[3 * kMaxPartialBlocks] + pb[4 * kMaxPartialBlocks] + pb[5 * kMaxPartialBlocks];
+    }
+    rr = wave_sum(rr);
+    bb = wave_sum(bb);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    if (lane == 0) {
+        sh[w] = rr;
+        sh[16 + w] = bb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) check_one(sh, nw, rtol, last_cycle, scal, istat, role, log);
+    if (host) {
+        __syncthreads();
+        status_to_host(scal, istat, host);
+    }
+}
+
 // Convergence checks of the two flow solves of a step in one launch (flow_check.h); one block
 // per instance.
 template <bool BATCH>
 __global__ __launch_bounds__(1024) void k_check_flow(int nblocks, int mode, ChkArgs one,
                                                     const ChkArgs* __restrict__ tab) {
     const ChkArgs& a = inst_args<BATCH>(one, tab, (int)blockIdx.x);
-    if (a.gate && *a.gate) return;
     __shared__ double sh[4 * 16];
-    flow_check_block(a.part, nblocks, a.rtol, a.scal, a.istat, sh, mode, a.log);
+    if (!(a.gate && *a.gate)) flow_check_block(a.part, nblocks, a.rtol, a.scal, a.istat, sh, mode, a.log);
+    if (a.host) status_to_host(a.scal, a.istat, a.host);
 }
 
 }  // namespace
@@ -1245,10 +1253,10 @@ void launch_check_flow(hipStream_t s, const Dims& d, const double* partials, dou
 
 void launch_check(hipStream_t s, const double* partials, int nblocks, double rtol, int cycle,
                   int last_cycle, double* scal, int* istat, const int* gate, int slot0, int role,
-                  double* log) {
+                  double* log, char* host) {
     (void)cycle;
     launch_kernel(k_check, dim3(1), dim3(1024), 0, s, partials, nblocks, rtol,
-                       last_cycle, scal, istat, gate, slot0, role, log);
+                       last_cycle, scal, istat, gate, slot0, role, log, host);
 }
 
 }  // namespace vs

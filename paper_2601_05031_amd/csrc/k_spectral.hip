@@ -148,6 +148,7 @@ __global__ __launch_bounds__(kBlock) void k_rhs_dht_z(Dims d, FftPlan pz,
                                                      CPtr3 u, int correct, SPtr3<ST> spec,
                                                      const int* gate, int rpb) {
     if (gate && *gate) return;
+    if (rhs.reset && blockIdx.x + blockIdx.y + threadIdx.x == 0) clear_status(rhs.scal, rhs.reset);
     __shared__ double2 A[kTileElems];
     const int n = d.nz;
     const int nlines = rpb >> 1;
@@ -392,6 +393,7 @@ __global__ __launch_bounds__(64) void k_rhs_hz(Dims d, const double2* __restrict
                                               RhsArgs rhs, CPtr3 u, int correct, SPtr3<ST> spec,
                                               const int* gate) {
     if (gate && *gate) return;
+    if (rhs.reset && blockIdx.x + blockIdx.y + threadIdx.x == 0) clear_status(rhs.scal, rhs.reset);
     using P = TwoPass<B, A>;
     constexpr int N = P::N;
     constexpr int L = P::L;

@@ -97,6 +97,11 @@ enum CheckMode {
     CK_HALT = 2               // IS_HALT: every later kernel of the call exits at once and the
                               // host takes the correction cycles of this step
 };
+// The host copy of the scalars and status words (pinned memory that the kernels write): scal, then
+// istat, each padded as in the workspace.
+constexpr size_t kHostStatIst = 256;
+static_assert(SC_NSCAL * sizeof(double) <= kHostStatIst, "host status layout");
+constexpr size_t kHostStatBytes = kHostStatIst + IS_NSTAT * sizeof(int);
 // The per-step log: a ring of kLogCap records of kLogFields doubles (VS_L_* in include/vs.h),
 // one per time step (and one for the initial solve), written by the step's final flow check.
 constexpr int kLogCap = VS_LOG_CAP;
@@ -111,6 +116,8 @@ enum RhsMode {
 struct RhsArgs {
     int mode;
     const double* f[3];      // RHS_FIELD arrays, or omega for RHS_NEGW
+    double* scal;            // with reset: the residual scalars and
+    int* reset;              // the status words to clear (a lone solve's first cycle), or null
 };
 
 // Plan of a length-n transform: radices applied in order (Stockham passes).
@@ -192,6 +199,8 @@ struct AdvArgs {
     int ck_mode;             // CheckMode of that check
     double* ck_log;          // the per-step log that check appends to
     const int* gate;         // skip when *gate != 0 (a halted call), or null
+    int* reset;              // the status words, to clear them and the residual scalars (the
+                             // first step of a call, which takes no check), or null
 };
 void launch_advance(hipStream_t s, const Dims& d, Prec pr, const Over<AdvArgs>& a);
 int resid_flow_blocks(const Dims& d);
@@ -236,7 +245,12 @@ void launch_source(hipStream_t s, const Dims& d, Prec pr, const Over<SrcArgs>& a
 void launch_fill_profile(hipStream_t s, const Dims& d, double* dst, const double* prof);
 // Zero the wall rows j = 0, ny-1 of nf <= 6 fields in one launch.
 void launch_zero_walls(hipStream_t s, const Dims& d, double* const f[], int nf);
-void launch_reset_stats(hipStream_t s, double* scal, int* istat);
+// Clears the status words and residual scalars of the n pairs in tab (device memory).
+struct StatPtrs {
+    double* scal;
+    int* istat;
+};
+void launch_reset_stats(hipStream_t s, const StatPtrs* tab, int n);
 
 // ---------------------------------------------------------------- spectral Poisson
 // Spectral pipeline. The spectral intermediates are stored as double, or as float in the
@@ -295,6 +309,8 @@ struct ChkArgs {
     double rtol;
     const int* gate;
     double* log;         // the per-step log (the step's final check appends a record), or null
+    char* host;          // the host copy of the status, written by the check (also by one that is
+                         // gated off), or null
 };
 // Residuals of both flow problems at the current (or predicted) fields, stored in FP32 for the
 // refined mode's defect-correction cycle: vorticity into spec, stream vector into spec2.
@@ -421,7 +437,8 @@ int resid_flow_blocks(const Dims& d);
 void launch_diagnostics(hipStream_t s, const Dims& d, const double* phi, double* const omega[3],
                         double* const psi[3], const double* prof, double vz_lo, double vz_hi,
                         double eta, int model, double eps, double sigma, double* sigma_t,
-                        double* part, double* scal, double* const vscratch[3]);
+                        double* part, double* scal, double* const vscratch[3], const int* istat,
+                        char* host);
 // omega_x += dprof[ny + j], psi_x += dprof[j] at every node (a wall-speed change).
 void launch_shift_profiles(hipStream_t s, const Dims& d, double* omega_x, double* psi_x,
                            const double* dprof);
@@ -432,7 +449,7 @@ void launch_adj_mu2(hipStream_t s, const Dims& d, const double* phi, const doubl
                     const double* gbar, const double* scal, int model, double C_b, double eps,
                     double sigma, double dt, double mobility, double rate_V, double k_A,
                     double* phibar, double* part, bool mu1_ran, bool psi_from_source,
-                    double* scal_out);
+                    double* scal_out, const int* istat, char* host);
 // Residual-norm partials of a solve into slots slot0 .. slot0+5.
 void launch_resid_norm(hipStream_t s, const Dims& d, const RhsArgs& rhs,
                        const double* const u[3], int ncomp, double* partials, const int* gate,
@@ -445,7 +462,7 @@ void launch_check_flow(hipStream_t s, const Dims& d, const double* partials, dou
 // stream-vector solve of a step (its final check appends the step's record to log).
 void launch_check(hipStream_t s, const double* partials, int nblocks, double rtol, int cycle,
                   int last_cycle, double* scal, int* istat, const int* gate, int slot0 = 0,
-                  int role = 0, double* log = nullptr);
+                  int role = 0, double* log = nullptr, char* host = nullptr);
 
 
 }  // namespace vs
