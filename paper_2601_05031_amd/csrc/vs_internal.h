@@ -359,6 +359,8 @@ void launch_hx(hipStream_t s, const Dims& d, const FftPlan& px, bool f32, int nc
                const Over<HxArgs>& a);
 // corr: the correction form (homogeneous walls, stream-vector residual modes in spec2).
 void launch_tri_pair(hipStream_t s, const Dims& d, bool f32, bool corr, const Over<TriArgs>& a);
+// Its segmented form (k_tri_pair.hip); false (nothing launched) for other row counts.
+bool seg_tri_pair(hipStream_t s, const Dims& d, bool f32, bool corr, const Over<TriArgs>& a);
 // f32src: S stored as float (the refined mode).
 void launch_resid_flow_over(hipStream_t s, const Dims& d, bool f32src, const Over<ResArgs>& a);
 // mode: a CheckMode.
