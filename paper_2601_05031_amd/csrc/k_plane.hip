@@ -131,7 +131,9 @@ struct PlaneShape {
 // during the transforms, the rest during the stores (the whole plane beside a transform pass
 // would not fit in the registers). The twiddles sit in LDS, so no global load inside the
 // transforms waits behind the prefetch.
-template <int BX, int AX, int BZ, int AZ, bool ZFIRST, bool BATCH>
+// RHS (with ZFIRST): the right-hand side of a direct solve, z.sgn times the field minus the wall
+// terms, which the planes j = 1 and j = M take from the wall rows of z.wall.
+template <int BX, int AX, int BZ, int AZ, bool ZFIRST, bool BATCH, bool RHS = false>
 __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, AX, BZ, AZ>::WPE)) void k_hxz_plane(
     Dims d, int nc, ZArgs zone, const ZArgs* __restrict__ ztab, HxArgs xone,
     const HxArgs* __restrict__ xtab, int nplanes) {
@@ -194,8 +196,36 @@ __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, A
             const int i = t / (NZ / 2), k2 = t - i * (NZ / 2);
             v[r] = ldg2(in + i * pstride + 2 * k2);
         }
+        if constexpr (RHS) {
+            const int cg = p / d.M, j = 1 + (p - cg * d.M);
+            const double sg = zone.sgn;
+            const bool wall = j == 1 || j == d.M;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                if (r < r0 || r >= r1) continue;
+                v[r].x *= sg;
+                v[r].y *= sg;
+                if (!wall) continue;
+                const int t = min((int)threadIdx.x + r * NT, NV - 1);
+                const int i = t / (NZ / 2), k2 = t - i * (NZ / 2);
+                const Gl<double>* w = (const Gl<double>*)pick(zone.wall, cg) + i * pstride + 2 * k2;
+                if (j == 1) {
+                    const double2 u = ldg2(w);
+                    v[r].x -= u.x * d.inv_h2;
+                    v[r].y -= u.y * d.inv_h2;
+                }
+                if (j == d.M) {
+                    const double2 u = ldg2(w + (size_t)(d.ny - 1) * NZ);
+                    v[r].x -= u.x * d.inv_h2;
+                    v[r].y -= u.y * d.inv_h2;
+                }
+            }
+        }
     };
     int p = live(blockIdx.x);
+    if constexpr (RHS) {
+        if (zone.reset && blockIdx.x + threadIdx.x == 0) clear_status(zone.scal, zone.reset);
+    }
     if (PF && p < nplanes) load(p, 0, NR);
     while (p < nplanes) {
         if (!PF) load(p, 0, NR);
@@ -455,7 +485,10 @@ void plane_go(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<Z
         if (z.tab) launch_kernel(kt, g, blk, 0, s, d, ncomp, z.one, z.tab, x.one, x.tab, nplanes);
         else launch_kernel(kf, g, blk, 0, s, d, ncomp, z.one, z.tab, x.one, x.tab, nplanes);
     };
-    if (zfirst) go(k_hxz_plane<BX, AX, BZ, AZ, true, false>, k_hxz_plane<BX, AX, BZ, AZ, true, true>);
+    if (zfirst && z.one.wall[0] && !z.tab)
+        launch_kernel((k_hxz_plane<BX, AX, BZ, AZ, true, false, true>), g, blk, 0, s, d, ncomp, z.one, z.tab,
+                      x.one, x.tab, nplanes);
+    else if (zfirst) go(k_hxz_plane<BX, AX, BZ, AZ, true, false>, k_hxz_plane<BX, AX, BZ, AZ, true, true>);
     else go(k_hxz_plane<BX, AX, BZ, AZ, false, false>, k_hxz_plane<BX, AX, BZ, AZ, false, true>);
 }
 

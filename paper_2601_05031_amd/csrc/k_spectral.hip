@@ -276,9 +276,16 @@ struct TwoPass {
 // Prep: Pre prep(line) (per-line row offsets, computed once per item).
 // Loader: double2 load(pre, k1, k2) -> (line a value, line b value) at position k1 + A k2.
 // Storer: void store(pre, p, ha, hb).
-template <int B, int A, bool LINE_FAST, class T, class P, class Prep, class Load, class Store>
+// Adj: void adj(pre, k1, x) changes the B loaded values of an item (in a block of its own, so that no
+// branch stands between their loads).
+struct NoAdj {
+    template <class Pre, class C>
+    __device__ __forceinline__ void operator()(const Pre&, int, C*) const {}
+};
+template <int B, int A, bool LINE_FAST, class T, class P, class Prep, class Load, class Store,
+          class Adj = NoAdj>
 __device__ __forceinline__ void two_pass_hartley(C2<T>* Y, const double2* __restrict__ tw_,
-                                                 Prep prep, Load load, Store store) {
+                                                 Prep prep, Load load, Store store, Adj adj = Adj{}) {
     // the twiddle table is global memory (typed so, whatever the pointer's origin)
     const Gl<tw2v>* __restrict__ tw = (const Gl<tw2v>*)tw_;
     using C = C2<T>;
@@ -292,6 +299,7 @@ __device__ __forceinline__ void two_pass_hartley(C2<T>* Y, const double2* __rest
         C x[B];
 #pragma unroll
         for (int k2 = 0; k2 < B; ++k2) x[k2] = load(pre, k1, k2);
+        adj(pre, k1, x);
         fftr::DFT<B>::run(x);
 #pragma unroll
         for (int p2 = 1; p2 < B; ++p2) x[p2] = cmul_tw<T>(x[p2], tw[k1 * p2]);
@@ -432,26 +440,31 @@ __global__ __launch_bounds__(64) void k_rhs_hz(Dims d, const double2* __restrict
             o.x = row_base(d, ra, nrows);
             o.y = row_base(d, rbb, nrows);
             const int ja = 1 + (ra - (ra / d.M) * d.M), jb = 1 + (rbb - (rbb / d.M) * d.M);
-            o.z = (ja == 1 ? 1 : 0) | (ja == d.M ? 2 : 0);
-            o.w = (jb == 1 ? 1 : 0) | (jb == d.M ? 2 : 0);
+            o.z = o.x < 0 ? 0 : (ja == 1 ? 1 : 0) | (ja == d.M ? 2 : 0);
+            o.w = o.y < 0 ? 0 : (jb == 1 ? 1 : 0) | (jb == d.M ? 2 : 0);
             return o;
         };
-        auto rowval = [&](int rb, int fl, int k) -> double {
-            if (rb < 0) return 0.0;
-            double b = sg * fc[rb + k];
-            if (fl & 1) b -= uc[rb - d.nz + k] * d.inv_h2;
-            if (fl & 2) b -= uc[rb + d.nz + k] * d.inv_h2;
-            return b;
-        };
+        // rows past the last one read the first row and are not stored
         auto load = [&](const int4& o, int k1, int k2) -> C {
             const int k = k1 + A * k2;
-            return mkc<T>((T)rowval(o.x, o.z, k), (T)rowval(o.y, o.w, k));
+            return mkc<T>((T)(sg * fc[max(o.x, 0) + k]), (T)(sg * fc[max(o.y, 0) + k]));
+        };
+        auto walls = [&](const int4& o, int k1, C* x) {
+            if (!(o.z | o.w)) return;
+#pragma unroll
+            for (int k2 = 0; k2 < B; ++k2) {
+                const int k = k1 + A * k2;
+                if (o.z & 1) x[k2].x = (T)((double)x[k2].x - uc[o.x - d.nz + k] * d.inv_h2);
+                if (o.z & 2) x[k2].x = (T)((double)x[k2].x - uc[o.x + d.nz + k] * d.inv_h2);
+                if (o.w & 1) x[k2].y = (T)((double)x[k2].y - uc[o.y - d.nz + k] * d.inv_h2);
+                if (o.w & 2) x[k2].y = (T)((double)x[k2].y - uc[o.y + d.nz + k] * d.inv_h2);
+            }
         };
         auto storew = [&](const int4& o, int p, T ha, T hb) {
             if (o.x >= 0) sc[o.x + p] = (ST)ha;
             if (o.y >= 0) sc[o.y + p] = (ST)hb;
         };
-        two_pass_hartley<B, A, false, T, P>(Y, tw, prepw, load, storew);
+        two_pass_hartley<B, A, false, T, P>(Y, tw, prepw, load, storew, walls);
         return;
     }
 #pragma unroll 4

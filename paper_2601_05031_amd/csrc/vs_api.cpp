@@ -401,12 +401,35 @@ void enqueue_verify(vs_state* S, const RhsArgs& rhs, double* const u[3], int nco
 }
 
 // One transform cycle: cycle 0 (correct = 0) solves directly from b and the wall rows;
-// a correction cycle solves for the correction of the residual and adds it to u.
+// a correction cycle solves for the correction of the residual and adds it to u. The direct cycle
+// takes the plane passes where the grid has them (128^3 scalar solve: 20.6 + 15.8 us against 41 + 20
+// us of line passes; the line form's wall terms, once a branch at every load, are applied after the
+// loads now).
 void enqueue_cycle(vs_state* S, const RhsArgs& rhs, double* const u[3], int ncomp, int correct,
                    int tag, const int* gate) {
     const Dims& d = S->d;
     const double* const cu[3] = {u[0], u[1], u[2]};
     const int k_rhs = tag == TAG_OMEGA ? K_RHS_Z_OMEGA : tag == TAG_PSI ? K_RHS_Z_PSI : K_RHS_Z_FIELD;
+    if (!correct && !S->f32 && !gate && tuning_for(d).plane && plane_fits(d)) {
+        // the direct cycle with one plane pass per direction
+        ZArgs zf{}, zi{};
+        HxArgs x{};
+        for (int c = 0; c < ncomp; ++c) {
+            zf.spec[c] = (void*)rhs.f[c];
+            zf.wall[c] = u[c];
+            zi.u[c] = u[c];
+            x.spec[c] = S->spec[c];
+        }
+        zf.tw = zi.tw = S->twz;
+        x.tw = S->twx;
+        zf.sgn = rhs.mode == RHS_NEGW ? -1.0 : 1.0;
+        zf.scal = rhs.scal;
+        zf.reset = rhs.reset;
+        timed(S, K_DHT_ZX, [&] { launch_plane(S->stream, d, true, ncomp, over_one(zf), over_one(x)); });
+        timed(S, K_TRIDIAG_Y, [&] { launch_tridiag_y(S->stream, d, S->tri, S->spec, ncomp, false, nullptr); });
+        timed(S, K_DHT_XZ_PAIR, [&] { launch_plane(S->stream, d, false, ncomp, over_one(zi), over_one(x)); });
+        return;
+    }
     timed(S, k_rhs, [&] {
         launch_rhs_dht_z(S->stream, d, S->pz, S->twz, rhs, cu, ncomp, correct, S->spec, S->f32, gate);
     });
@@ -1750,22 +1773,19 @@ vs_status autotune_state(vs_state* S, Tuning* picked) {
         launch_va_partials(c.st, c.d, A.va);
         launch_mu(c.st, c.d, c.model, pr, A.mu);
     });
-    // the chemical potential's form: LDS tiles, or register marching (where a row fits a wave)
-    // with 1 or 2 rows per lane group and 2 .. 16 planes per slab, as one coordinate
-    {
-        const bool reg_ok = mu_reg_zpl(S->d) > 0;
-        const int cand[][2] = {{0, 8}, {1, 2}, {1, 4}, {1, 8}, {1, 16}, {2, 2}, {2, 4}, {2, 8}, {2, 16}};
+    // the chemical potential where a row fits a wave (the LDS tiles were slower on all 10 such grids
+    // of the sweep behind default_tuning): 1 or 2 rows per lane group and 2 .. 16 planes per slab, as one coordinate
+    if (mu_reg_zpl(S->d) > 0) {
+        const int cand[][2] = {{1, 2}, {1, 4}, {1, 8}, {1, 16}, {2, 2}, {2, 4}, {2, 8}, {2, 16}};
         int bk = t.mu_kind, bn = t.mu_ni;
         float tb = 1e30f;
         for (const auto& cd : cand) {
-            if (cd[0] > 0 && !reg_ok) continue;
+            // slabs that leave half the CUs without a block never win
+            if (cd[1] > 2 && mu_reg_blocks(S->d, cd[0], cd[1]) < 128) continue;
             t.mu_kind = cd[0];
             t.mu_ni = cd[1];
             set_tuning(S->d, t);
-            const float ms = time([&] {
-                launch_va_partials(c.st, c.d, A.va);
-                launch_mu(c.st, c.d, c.model, pr, A.mu);
-            });
+            const float ms = time([&] { launch_mu(c.st, c.d, c.model, pr, A.mu); });
             if (ms < tb) {
                 tb = ms;
                 bk = cd[0];

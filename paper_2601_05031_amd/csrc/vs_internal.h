@@ -275,6 +275,12 @@ struct ZArgs {
     const int* hist;
     int* hist_out;
     int self;            // refined mode: transform FP32 spec in place (the forward z pass)
+    // forward plane pass of a direct solve's right-hand side: sgn * spec minus the wall terms of
+    // these fields (or null: spec alone); reset as in RhsArgs
+    const double* wall[3];
+    double sgn;
+    double* scal;
+    int* reset;
 };
 // x transforms, in place on spec[c], c < ncomp <= 6.
 struct HxArgs {
