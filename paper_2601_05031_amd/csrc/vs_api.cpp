@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -1590,6 +1591,8 @@ struct BlobHeader {
     double u0, u1;            // wall speeds
     double scal[SC_NSCAL];
 };
+static_assert(offsetof(BlobHeader, scal) == kStateHeadWords * 8 && sizeof(BlobHeader) % 16 == 0,
+              "the header's fixed words, then the scalars, then 16-byte aligned fields");
 
 // Whether p points into device memory (a checkpoint may live on the device: then every copy
 // stays on the device). Host memory the runtime does not know reports an error: cleared.
@@ -1603,6 +1606,19 @@ bool device_blob(const void* p) {
 }
 }  // namespace
 
+namespace {
+// Whether a device blob is copied by one launch (k_state.hip): on the state's device and aligned for
+// 16-byte values. Others take the runtime's copies.
+bool one_launch(const vs_state* S, const void* blob) {
+    if ((uintptr_t)blob % 16) return false;
+    hipPointerAttribute_t a{}, b{};
+    const bool ok = hipPointerGetAttributes(&a, blob) == hipSuccess &&
+                    hipPointerGetAttributes(&b, S->ws) == hipSuccess && a.device == b.device;
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+}  // namespace
+
 vs_status vs_save_state(vs_state* S, void* blob, size_t* bytes) {
     if (!S) return fail(VS_E_STATE, "state is NULL");
     if (!bytes) return fail(VS_E_ARG, "bytes is NULL");
@@ -1613,7 +1629,6 @@ vs_status vs_save_state(vs_state* S, void* blob, size_t* bytes) {
         return VS_OK;
     }
     if (*bytes < need) return fail(VS_E_ARG, "blob has %zu bytes, needs %zu", *bytes, need);
-    HIP_TRY(hipStreamSynchronize(S->stream));
     const bool dev = device_blob(blob);
     BlobHeader hd{};
     std::memcpy(hd.magic, "VSSTATE2", 8);
@@ -1624,13 +1639,33 @@ vs_status vs_save_state(vs_state* S, void* blob, size_t* bytes) {
     hd.step = S->step;
     hd.u0 = S->w.u0;
     hd.u1 = S->w.u1;
+    const double* src[8] = {S->phi[S->cur], S->mu, S->om[0], S->om[1], S->om[2], S->ps[0], S->ps[1], S->ps[2]};
+    if (dev && one_launch(S, blob)) {
+        StateCopy a{};
+        double* dst = (double*)((char*)blob + sizeof hd);
+        for (int q = 0; q < 8; ++q) {
+            a.src[q] = src[q];
+            a.dst[q] = dst + q * N;
+        }
+        a.scal_src = S->scal;
+        a.scal_dst = (double*)((char*)blob + offsetof(BlobHeader, scal));
+        std::memcpy(a.head, &hd, sizeof a.head);
+        a.head_dst = (unsigned long long*)blob;
+        // work on the default stream may still use the blob's memory (a caching allocator's)
+        if (S->stream) HIP_TRY(hipStreamSynchronize(nullptr));
+        launch_state_copy(S->stream, a, N);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(S->stream));
+        *bytes = need;
+        return VS_OK;
+    }
+    HIP_TRY(hipStreamSynchronize(S->stream));
     HIP_TRY(hipMemcpy(hd.scal, S->scal, sizeof hd.scal, hipMemcpyDeviceToHost));
     if (dev)
         HIP_TRY(hipMemcpy(blob, &hd, sizeof hd, hipMemcpyHostToDevice));
     else
         std::memcpy(blob, &hd, sizeof hd);
     double* dst = (double*)((char*)blob + sizeof hd);
-    const double* src[8] = {S->phi[S->cur], S->mu, S->om[0], S->om[1], S->om[2], S->ps[0], S->ps[1], S->ps[2]};
     for (int q = 0; q < 8; ++q)
         HIP_TRY(hipMemcpyAsync(dst + q * N, src[q], N * sizeof(double),
                                dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, S->stream));
@@ -1657,14 +1692,28 @@ vs_status vs_load_state(vs_state* S, const void* blob, size_t bytes) {
     HIP_TRY(hipStreamSynchronize(S->stream));
     const double* src = (const double*)((const char*)blob + sizeof hd);
     double* dst[8] = {S->phi[S->cur], S->mu, S->om[0], S->om[1], S->om[2], S->ps[0], S->ps[1], S->ps[2]};
-    for (int q = 0; q < 8; ++q)
-        HIP_TRY(hipMemcpyAsync(dst[q], src + q * N, N * sizeof(double),
-                               dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
-    HIP_TRY(hipStreamSynchronize(S->stream));
-    HIP_TRY(hipMemcpy(S->scal, hd.scal, sizeof hd.scal, hipMemcpyHostToDevice));
     // the checkpoint holds no time increments: the refined mode's predictor starts over
-    const int no_hist[2] = {0, 0};
-    HIP_TRY(hipMemcpy(S->istat + IS_HIST, no_hist, sizeof no_hist, hipMemcpyHostToDevice));
+    if (dev && one_launch(S, blob)) {
+        StateCopy a{};
+        for (int q = 0; q < 8; ++q) {
+            a.src[q] = src + q * N;
+            a.dst[q] = dst[q];
+        }
+        a.scal_src = (const double*)((const char*)blob + offsetof(BlobHeader, scal));
+        a.scal_dst = S->scal;
+        a.hist = S->istat + IS_HIST;
+        launch_state_copy(S->stream, a, N);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(S->stream));
+    } else {
+        for (int q = 0; q < 8; ++q)
+            HIP_TRY(hipMemcpyAsync(dst[q], src + q * N, N * sizeof(double),
+                                   dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
+        HIP_TRY(hipStreamSynchronize(S->stream));
+        HIP_TRY(hipMemcpy(S->scal, hd.scal, sizeof hd.scal, hipMemcpyHostToDevice));
+        const int no_hist[2] = {0, 0};
+        HIP_TRY(hipMemcpy(S->istat + IS_HIST, no_hist, sizeof no_hist, hipMemcpyHostToDevice));
+    }
     S->step = hd.step;
     S->gamma_host = hd.scal[SC_GAMMA];
     if (hd.u0 != S->w.u0 || hd.u1 != S->w.u1) {

@@ -252,6 +252,21 @@ struct StatPtrs {
 };
 void launch_reset_stats(hipStream_t s, const StatPtrs* tab, int n);
 
+// ---------------------------------------------------------------- checkpoints
+// Copies eight fields of n doubles (16-byte aligned, n even) and the scalars; on a save also the
+// header's fixed words, on a load the reset of the predictor's two history words.
+constexpr int kStateHeadWords = 6;
+struct StateCopy {
+    const double* src[8];
+    double* dst[8];
+    const double* scal_src;
+    double* scal_dst;
+    unsigned long long head[kStateHeadWords];
+    unsigned long long* head_dst;   // or null
+    int* hist;                      // or null
+};
+void launch_state_copy(hipStream_t s, const StateCopy& a, size_t n);
+
 // ---------------------------------------------------------------- spectral Poisson
 // Spectral pipeline. The spectral intermediates are stored as double, or as float in the
 // refined mode; the two-pass transforms and the segmented tridiagonal solves compute in the

@@ -389,10 +389,10 @@ def rollout_gradient(solver: "Solver", dt: float, nsteps: int, target, checkpoin
     torch = solver.torch
     ce = max(1, int(checkpoint_every))
     ckpt = {0: solver.save(device=True)}   # checkpoints stay in HBM
-    for n in range(nsteps):
-        solver.step(dt, 1)
-        if (n + 1) % ce == 0:
-            ckpt[n + 1] = solver.save(device=True)
+    for n in range(0, nsteps, ce):
+        solver.step(dt, min(ce, nsteps - n))
+        if n + ce <= nsteps:
+            ckpt[n + ce] = solver.save(device=True)
     r = solver.field("phi") - target
     loss = float((r * r).sum())
     a = (2.0 * r).contiguous()

@@ -148,3 +148,31 @@ def test_reverse_step_that_misses_takes_the_general_path():
         assert out["d"][0] == pytest.approx(k0, rel=1e-9) and out["d"][1] == pytest.approx(s0, rel=1e-9, abs=1e-18)
     s.close()
     t.close()
+
+
+# one launch for an aligned device blob, the runtime's copies for any other: the same bytes
+@pytest.mark.parametrize("precision,shape", [("fp64", (12, 7, 18)), ("fp32_refined", (32, 9, 48))])
+def test_device_checkpoints_are_the_host_checkpoints(precision, shape):
+    w = case(shape, 1).with_(max_cycles=3)
+    s = P.solver_for(w, precision=precision)
+    s.step(w.dt, 3)
+    host, dev = s.save(), s.save(device=True)
+    assert bytes(dev.cpu().numpy()) == host
+    odd = torch.empty(dev.numel() + 8, dtype=torch.uint8, device="cuda")[8:]   # 8-byte aligned only
+    import ctypes
+    n = ctypes.c_size_t(odd.numel())
+    assert V.lib().vs_save_state(s._st, ctypes.c_void_p(odd.data_ptr()), ctypes.byref(n)) == V.VS_OK
+    assert bytes(odd.cpu().numpy()) == host
+    s.step(w.dt, 2)
+    after = s.fields(), s.scalars()
+    for blob in (host, dev, odd):
+        s.load(blob)
+        if precision == "fp64":
+            assert s.save() == host
+        s.step(w.dt, 2)
+        got = s.fields(), s.scalars()
+        for k in FIELD_NAMES:
+            # the refined mode's time extrapolation starts over at a load (its solve tolerance)
+            assert np.array_equal(got[0][k], after[0][k]) if precision == "fp64" else rel_l2(got[0][k], after[0][k]) <= 1e-6
+        assert got[1]["step"] == after[1]["step"]
+    s.close()
