@@ -68,7 +68,7 @@ def source_hash(kernel: str) -> str:
     """Hash of the code (comments aside) of the source files that hold a kernel, to tie
     stored counters to the code they were taken on."""
     names = (["k_explicit.hip", "stencil.h"] if kernel in ("advance", "va_partials", "mu", "source")
-             else ["k_spectral.hip", "k_plane.hip", "k_tri.hip", "k_tri_pair.hip", "tri_seg.h", "k_solve.hip", "spectral.h", "fft_reg.h", "flow_check.h"])
+             else ["k_spectral.hip", "k_plane.hip", "k_plane_any.hip", "k_tri.hip", "k_tri_pair.hip", "tri_seg.h", "k_solve.hip", "spectral.h", "fft_reg.h", "flow_check.h"])
     h = hashlib.sha256()
     for fname in names:
         with open(os.path.join(ROOT, "paper_2601_05031_amd", "csrc", fname)) as f:

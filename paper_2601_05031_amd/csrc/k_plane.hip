@@ -467,10 +467,12 @@ int plane_blocks() {
     return n;
 }
 
-bool plane_fits(const Dims& d) {
+// The grids with kernels of their own; the others take launch_plane_any where it fits.
+static bool plane_own(const Dims& d) {
     auto len = [](int n) { return n == 32 || n == 48 || n == 64 || n == 96 || n == 128; };
     return len(d.nx) && len(d.nz);
 }
+bool plane_fits(const Dims& d) { return plane_own(d) || plane_any_fits(d); }
 
 namespace {
 
@@ -510,6 +512,10 @@ bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Ov
                   const Over<HxArgs>& x) {
     if (!plane_fits(d) || ncomp < 1 || ncomp > 6 || z.one.add) return false;
     if ((z.tab != nullptr) != (x.tab != nullptr) || (z.tab && z.n != x.n)) return false;
+    if (!plane_own(d)) {
+        launch_plane_any(s, d, zfirst, ncomp, z, x);
+        return true;
+    }
     switch (d.nx) {
     case 32: plane_go_x<8, 4>(s, d, zfirst, ncomp, z, x); break;
     case 48: plane_go_x<16, 3>(s, d, zfirst, ncomp, z, x); break;
@@ -523,7 +529,7 @@ bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Ov
 // The refined mode's FP32 plane forms: square planes of n_x = n_z in {32, 48, 64, 96, 128}
 // and the 128 x 256 plane (132 KB of floats).
 bool plane32_fits(const Dims& d) {
-    return (d.nx == d.nz && plane_fits(d)) || (d.nx == 128 && d.nz == 256);
+    return (d.nx == d.nz && plane_own(d)) || (d.nx == 128 && d.nz == 256);
 }
 
 bool launch_plane32(hipStream_t s, const Dims& d, bool zfirst, const Over<ZArgs>& z,

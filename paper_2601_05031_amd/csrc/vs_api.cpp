@@ -309,7 +309,8 @@ std::vector<TuneEntry> g_tune;
 //            of 16, 8, 4, 2 planes that fills the CUs at once (two blocks per CU, one at four z
 //            per lane): 64^3 6.7 us at 2 planes (LDS tiles 10.1), 128^3 11.1 at 4 (16.6),
 //            128 x 128 x 256 20.7 at 8 (31.0), 256^3 63 at 16 (104);
-//  plane     both transforms of a direction in one pass wherever the plane fits in LDS (k_plane.hip).
+//  plane     both transforms of a direction in one pass wherever plane_fits (k_plane.hip,
+//            k_plane_any.hip).
 // The partials' block caps and the tridiagonal layout are best or within 3% at their defaults.
 Tuning default_tuning(const Dims& d) {
     Tuning t{2, 1024, 1024, 0, 0, 8, plane_fits(d) ? 1 : 0};

@@ -369,9 +369,14 @@ bool refined_ok(const Dims& d);
 // Both transform directions in one pass per (interior row, component), the (x, z) plane in
 // LDS: zfirst, z then x from z.spec into x.spec (the source's forward transform); otherwise x
 // then z from x.spec into z.u (the inverse of the omega and psi modes). FP64 spectral data,
-// n_x and n_z in {32, 48, 64, 96, 128}, no accumulation, gated per instance by z.gate; returns
+// planes that fit in LDS (plane_fits), no accumulation, gated per instance by z.gate; returns
 // false (nothing launched) otherwise.
 bool plane_fits(const Dims& d);
+int plane_blocks();   // compute units of the current device
+// The same passes for the lengths without a kernel of their own (k_plane_any.hip).
+bool plane_any_fits(const Dims& d);
+void launch_plane_any(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,
+                      const Over<HxArgs>& x);
 bool launch_plane(hipStream_t s, const Dims& d, bool zfirst, int ncomp, const Over<ZArgs>& z,
                   const Over<HxArgs>& x);
 void launch_hz(hipStream_t s, const Dims& d, const FftPlan& pz, bool f32, int ncomp,

@@ -90,3 +90,42 @@ def test_a_batch_with_oblong_planes_is_bitwise_the_single_states():
         s.close()
         for k in FIELD_NAMES:
             assert np.array_equal(got[k], ref[k]), k
+
+
+# the planes of lengths that share one kernel: idle lanes, several rounds of lines, short last rounds;
+# one component (a Poisson solve, walls in the load) and three and six (a step), single and batched
+ANY = [(16, 16), (16, 108), (24, 36), (36, 24), (54, 54), (72, 72), (72, 108), (108, 72), (32, 72), (108, 16)]
+
+
+@pytest.mark.parametrize("nx,nz", ANY)
+def test_planes_of_other_lengths_match_line_transforms(nx, nz):
+    shape = (nx, 7, nz)
+    w = case(shape, "droplet256" if nx > nz else "vesicle32", mc=1 if nx % 3 else 3)
+    print(f"case plane any {shape}", flush=True)
+    ref, got = run(w, LINES), run(w, dict(LINES, plane=1))
+    errs = {k: rel_l2(got[k], ref[k]) for k in FIELD_NAMES}
+    print("  " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()), flush=True)
+    assert max(errs.values()) <= 1e-12, errs
+    rng = np.random.default_rng(nx + nz)
+    f, u0 = rng.standard_normal(shape), rng.standard_normal(shape)
+    sols = []
+    for plane in (0, 1):
+        V.set_launch_shapes(shape + (1.0,), dict(LINES, plane=plane))
+        s = P.solver_for(w)
+        ft, ut = torch.tensor(f, device="cuda"), torch.tensor(u0, device="cuda")
+        code, cycles, rel = s.poisson_solve(ft, ut, rtol=1e-12, max_cycles=2)
+        s.close()
+        assert code == V.VS_OK and cycles == 1
+        sols.append(ut.cpu().numpy())
+    assert rel_l2(sols[1], sols[0]) <= 1e-12
+    solvers = [P.solver_for(w), P.solver_for(w)]
+    b = V.Batch(solvers)
+    b.step([w.dt, w.dt], 2)
+    b.close()
+    for s in solvers:
+        s.step(w.dt, 1)
+        f3 = s.fields()
+        s.close()
+        for k in FIELD_NAMES:
+            assert np.array_equal(f3[k], got[k]), k
+    V.set_launch_shapes(shape + (1.0,), LINES)
