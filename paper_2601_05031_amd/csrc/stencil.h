@@ -88,32 +88,11 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], double* sh) {
 
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
-// Velocity components at a node: curl psi on the interior rows, the wall speed on the walls.
+// The velocity's fields: curl psi on the interior rows, the wall speed on the walls.
 struct Vel {
     const double *px, *py, *pz;
     double vz_lo, vz_hi;
 };
-
-__device__ __forceinline__ double vx_at(const Vel& v, const Dims& d, int i, int j, int k) {
-    if (j == 0 || j == d.ny - 1) return 0.0;
-    const int kp = wrap(k + 1, d.nz), km = wrap(k - 1, d.nz);
-    return ((v.pz[node(d, i, j + 1, k)] - v.pz[node(d, i, j - 1, k)]) -
-            (v.py[node(d, i, j, kp)] - v.py[node(d, i, j, km)])) * d.inv_2h;
-}
-__device__ __forceinline__ double vy_at(const Vel& v, const Dims& d, int i, int j, int k) {
-    if (j == 0 || j == d.ny - 1) return 0.0;
-    const int ip = wrap(i + 1, d.nx), im = wrap(i - 1, d.nx);
-    const int kp = wrap(k + 1, d.nz), km = wrap(k - 1, d.nz);
-    return ((v.px[node(d, i, j, kp)] - v.px[node(d, i, j, km)]) -
-            (v.pz[node(d, ip, j, k)] - v.pz[node(d, im, j, k)])) * d.inv_2h;
-}
-__device__ __forceinline__ double vz_at(const Vel& v, const Dims& d, int i, int j, int k) {
-    if (j == 0) return v.vz_lo;
-    if (j == d.ny - 1) return v.vz_hi;
-    const int ip = wrap(i + 1, d.nx), im = wrap(i - 1, d.nx);
-    return ((v.py[node(d, ip, j, k)] - v.py[node(d, im, j, k)]) -
-            (v.px[node(d, i, j + 1, k)] - v.px[node(d, i, j - 1, k)])) * d.inv_2h;
-}
 
 __device__ __forceinline__ double wrow(const Dims& d, int j) {
     return (j == 0 || j == d.ny - 1) ? 0.5 : 1.0;
