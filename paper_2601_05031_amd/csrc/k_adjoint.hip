@@ -11,7 +11,8 @@
 //   * the Poisson problems are self-adjoint with homogeneous walls (solved by the host driver
 //     with the forward solver); their wall values enter rows 1 and ny-2 with weight 1/h^2;
 //   * V (SM eq. (37)), A (SM eq. (32)) and the penalty multipliers are differentiated directly.
-// The node loops are plain one-node-per-lane stencils (the reverse step is off the timed path).
+#include <type_traits>
+
 #include "flow_check.h"
 #include "stencil.h"
 
@@ -492,20 +493,43 @@ __global__ __launch_bounds__(kBlock) void k_adj_mu1(const double* __restrict__ p
                                                    double* __restrict__ partials) {
     __shared__ double sh[2 * 16];
     double acc[2] = {0.0, 0.0};
-    const SlabIter it = slab_iter(d, sg);
+    const PairLane L = pair_lane(d, sg);
     const double eps2 = eps * eps;
-    if (it.ok) {
-        const int j = it.j, k = it.k;
-        for (int i = it.i0; i < it.i1; ++i) {
-            const Nbr n = neighbours_mirror(d, i, j, k);
-            const double p = phi[n.c];
-            const double mb = mubar[n.c];
-            const double lphi = lap7(phi, n, d.inv_h2);
-            const double gc = p * p * p - p - eps2 * lphi;
-            const double core = (3.0 * p * p - 1.0) * mb - eps2 * lapT(mubar, d, i, j, k);
-            gbar[n.c] = C_b * core;
-            acc[0] += dCb * gc * core;
-            acc[1] -= mb * lphi;
+    if (L.ok) {
+        const double wj = wrow(d, L.j);
+        const double rwm = 1.0 / wrow(d, L.j == 0 ? 1 : L.j - 1);
+        const double rwp = 1.0 / wrow(d, L.j + 1 == d.ny ? d.ny - 2 : L.j + 1);
+        size_t b = (size_t)wrap(L.i0 - 1, d.nx) * L.plane + L.o;
+        double2 pm = ldp(phi + b), mm = ldp(mubar + b);
+        b = (size_t)L.i0 * L.plane + L.o;
+        double2 pc = ldp(phi + b), mc = ldp(mubar + b);
+#pragma unroll 1
+        for (int i = L.i0; i < L.i1; ++i) {
+            const size_t c = (size_t)i * L.plane, bn = (size_t)wrap(i + 1, d.nx) * L.plane + L.o;
+            const double2 pyp = ldp(phi + c + L.oyp), pym = ldp(phi + c + L.oym);
+            const double2 myp = ldp(mubar + c + L.oyp), mym = ldp(mubar + c + L.oym);
+            const double pl = phi[c + L.ol], pr = phi[c + L.orr];
+            const double ml = mubar[c + L.ol], mr = mubar[c + L.orr];
+            const double2 pp = ldp(phi + bn), mp = ldp(mubar + bn);
+            __builtin_amdgcn_sched_barrier(0);
+            auto one = [&](double p, double pxp, double pxm, double p_yp, double p_ym, double pzp, double pzm,
+                           double mb, double mxp, double mxm, double m_yp, double m_ym, double mzp,
+                           double mzm) -> double {
+                const double lphi = (pxp + pxm + p_yp + p_ym + pzp + pzm - 6.0 * p) * d.inv_h2;
+                const double xz = mxp + mxm + mzp + mzm;
+                const double lt = (xz + wj * (m_yp * rwp + m_ym * rwm) - 6.0 * mb) * d.inv_h2;
+                const double gc = p * p * p - p - eps2 * lphi;
+                const double core = (3.0 * p * p - 1.0) * mb - eps2 * lt;
+                acc[0] += dCb * gc * core;
+                acc[1] -= mb * lphi;
+                return C_b * core;
+            };
+            double2 g;
+            g.x = one(pc.x, pp.x, pm.x, pyp.x, pym.x, pc.y, pl, mc.x, mp.x, mm.x, myp.x, mym.x, mc.y, ml);
+            g.y = one(pc.y, pp.y, pm.y, pyp.y, pym.y, pr, pc.x, mc.y, mp.y, mm.y, myp.y, mym.y, mr, mc.x);
+            *reinterpret_cast<double2*>(gbar + c + L.o) = g;
+            pm = pc; pc = pp;
+            mm = mc; mc = mp;
         }
     }
     block_sum<2>(acc, sh);
@@ -516,10 +540,13 @@ __global__ __launch_bounds__(kBlock) void k_adj_mu1(const double* __restrict__ p
 }
 
 // phibar += (d mu / d phi)^T mubar + lambda_bar d lambda_V/d phi + A_bar dA/d phi. Each lane
-// owns one (j, k) column and walks an x-slab with phi of the planes i-2 .. i+2 and mubar, gbar
-// of the planes i-1 .. i+1 in registers.
+// owns a pair of z of one row (any even n_z) and walks an x-slab with phi of the planes i-2 .. i+2
+// and mubar, gbar of the planes i-1 .. i+1 in registers; 16-byte loads, all of a plane's before
+// their first use. 96^3: 19.2 us with one node per lane, 11.6 now; k_adj_mu1 likewise 9.9 and 6.6.
+// Bound by the latency of the walk (28 MB and 21 MB from the cache take 4 to 6 us).
 // Sums of the reverse step's block partials (fixed order, the same in every block): nb_src
 // blocks of k_adj_source, nb_mu1 of k_adj_mu1 (0: not launched).
+typedef double Pair8 __attribute__((ext_vector_type(2), aligned(8)));
 struct AdjSums {
     const double* part;
     int nb_src, nb_mu1;
@@ -565,10 +592,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_mu2(const double* __restrict__ p
         __syncthreads();
         status_to_host(sums.scal, sums.istat, sums.host);
     }
-    const SlabIter it = slab_iter(d, sg);
-    if (!it.ok) return;
-    const int j = it.j, k = it.k, nz = d.nz;
-    const size_t plane = (size_t)d.ny * nz;
+    const PairLane L = pair_lane(d, sg);
+    if (!L.ok) return;
+    const int j = L.j, nz = d.nz;
     const bool ch = model == VS_CAHN_HILLIARD;
     const double w = wrow(d, j);
     const double h3 = d.h * d.h * d.h;
@@ -580,68 +606,105 @@ __global__ __launch_bounds__(kBlock) void k_adj_mu2(const double* __restrict__ p
     const double A0 = scal[SC_A0];
     const bool area = !ch && k_A != 0.0 && A0 > 0.0;
     const double Abar = area ? gamma_bar * k_A / A0 : 0.0;
-    const int kp = wrap(k + 1, nz), km = wrap(k - 1, nz);
-    const int kp2 = wrap(k + 2, nz), km2 = wrap(k - 2, nz);
+    // the pairs before and after (phi's z neighbours at distance two)
+    const int oL = j * nz + wrap(L.k - 2, nz), oR = j * nz + wrap(L.k + 2, nz);
     const int jm = (j == 0) ? 1 : j - 1, jp = (j == d.ny - 1) ? d.ny - 2 : j + 1;   // mirrored
-    const int o = j * nz + k, okm = j * nz + km, okp = j * nz + kp;
-    const int ojm = jm * nz + k, ojp = jp * nz + k;
     const double wj = wrow(d, j), rwm = 1.0 / wrow(d, jm), rwp = 1.0 / wrow(d, jp);
     const bool in_m = j >= 2, in_p = j <= d.ny - 3;   // rows j -/+ 1 interior
-    // L_h^T u at the node from the x-neighbours xm, xp and the plane base b
-    auto lapt = [&](const double* __restrict__ u, size_t b, double xm, double x0, double xp) {
-        const double xz = xp + xm + u[b + okp] + u[b + okm];
-        return (xz + wj * (u[b + ojp] * rwp + u[b + ojm] * rwm) - 6.0 * x0) * d.inv_h2;
+    const int oym2 = in_m ? L.o - 2 * nz : L.o, oyp2 = in_p ? L.o + 2 * nz : L.o;
+    // L_h^T u at a node from its neighbours
+    auto lapt = [&](double xp, double xm, double zp, double zm, double yp, double ym, double x0) {
+        const double xz = xp + xm + zp + zm;
+        return (xz + wj * (yp * rwp + ym * rwm) - 6.0 * x0) * d.inv_h2;
     };
-    auto ld = [&](const double* __restrict__ u, int ii) { return u[(size_t)ii * plane + o]; };
-    const int i0 = it.i0;
-    double pm2 = ld(phi, wrap(i0 - 2, d.nx)), pm1 = ld(phi, wrap(i0 - 1, d.nx)), p0 = ld(phi, i0);
-    double pp1 = ld(phi, wrap(i0 + 1, d.nx));
-    double mm = ld(mubar, wrap(i0 - 1, d.nx)), m0 = ld(mubar, i0);
-    double gm = 0.0, g0 = 0.0;
-    if (!ch) {
-        gm = ld(gbar, wrap(i0 - 1, d.nx));
-        g0 = ld(gbar, i0);
-    }
-    for (int i = i0; i < it.i1; ++i) {
-        const int ip = (i + 1 == d.nx) ? 0 : i + 1;
-        const double pp2 = ld(phi, wrap(i + 2, d.nx));
-        const double mp = ld(mubar, ip);
-        const double gp = ch ? 0.0 : ld(gbar, ip);
-        const size_t b = (size_t)i * plane;
-        const size_t c = b + o;
-        const double p = p0;
-        double r = r0;
-        if (ch) {
-            r += (3.0 * p * p - 1.0) * m0 - sigma * lapt(mubar, b, mm, m0, mp);
-        } else {
-            const double lphi = (pp1 + pm1 + phi[b + ojp] + phi[b + ojm] + phi[b + okp] + phi[b + okm] - 6.0 * p) * d.inv_h2;
-            const double gc = p * p * p - p - eps2 * lphi;
-            r += 6.0 * C_b * p * gc * m0 - gam * lapt(mubar, b, mm, m0, mp) +
-                 (3.0 * p * p - 1.0) * g0 - eps2 * lapt(gbar, b, gm, g0, gp);
-            if (area) {
-                // dA/dphi = 3/(2 sqrt 2) h^3 [eps sum_c D_c^T (w D_c phi) + w (phi^2 - 1) phi / eps]
-                const double dxm = (p - pm2) * d.inv_2h, dxp = (pp2 - p) * d.inv_2h;
-                const double dzm = (p - phi[b + j * nz + km2]) * d.inv_2h;
-                const double dzp = (phi[b + j * nz + kp2] - p) * d.inv_2h;
-                double div = w * ((dxm - dxp) + (dzm - dzp));
-                if (in_m) div += (p - phi[b + (j - 2) * nz + k]) * d.inv_2h;
-                if (in_p) div -= (phi[b + (j + 2) * nz + k] - p) * d.inv_2h;
-                const double dA = 3.0 / (2.0 * 1.4142135623730951) * h3 *
-                                  (eps * div * d.inv_2h + w * (p * p - 1.0) * p / eps);
-                r += Abar * dA;
-            }
+    auto ld = [&](const double* __restrict__ u, int ii) { return ldp(u + (size_t)ii * L.plane + L.o); };
+    const int i0 = L.i0;
+    double2 pm2 = ld(phi, wrap(i0 - 2, d.nx)), pm1 = ld(phi, wrap(i0 - 1, d.nx)), p0 = ld(phi, i0);
+    double2 pp1 = ld(phi, wrap(i0 + 1, d.nx));
+    double2 mm = ld(mubar, wrap(i0 - 1, d.nx)), m0 = ld(mubar, i0);
+    auto walk = [&](auto bc) {
+        constexpr bool BEND = decltype(bc)::value;
+        const double2 zero = make_double2(0.0, 0.0);
+        double2 gm = zero, g0 = zero;
+        if constexpr (BEND) {
+            gm = ld(gbar, wrap(i0 - 1, d.nx));
+            g0 = ld(gbar, i0);
         }
-        phibar[c] += r;
-        pm2 = pm1; pm1 = p0; p0 = pp1; pp1 = pp2;
-        mm = m0; m0 = mp;
-        gm = g0; g0 = gp;
-    }
+#pragma unroll 1
+        for (int i = i0; i < L.i1; ++i) {
+            const int ip = (i + 1 == d.nx) ? 0 : i + 1;
+            const size_t b = (size_t)i * L.plane;
+            const double2 myp = ldp(mubar + b + L.oyp), mym = ldp(mubar + b + L.oym);
+            const double ml = mubar[b + L.ol], mr = mubar[b + L.orr];
+            double2 gyp = zero, gym = zero, pyp = zero, pym = zero, pL = zero, pR = zero, py2 = zero, pn2 = zero;
+            double gl = 0.0, gr = 0.0;
+            if constexpr (BEND) {
+                gyp = ldp(gbar + b + L.oyp);
+                gym = ldp(gbar + b + L.oym);
+                gl = gbar[b + L.ol];
+                gr = gbar[b + L.orr];
+                pyp = ldp(phi + b + L.oyp);
+                pym = ldp(phi + b + L.oym);
+                pL = ldp(phi + b + oL);
+                pR = ldp(phi + b + oR);
+                if (area) {
+                    py2 = ldp(phi + b + oyp2);
+                    pn2 = ldp(phi + b + oym2);
+                }
+            }
+            Pair8* const out = reinterpret_cast<Pair8*>(phibar + b + L.o);   // the caller's: 8-byte aligned
+            const Pair8 old = *out;
+            const double2 pp2 = ld(phi, wrap(i + 2, d.nx));
+            const double2 mp = ld(mubar, ip);
+            const double2 gp = BEND ? ld(gbar, ip) : zero;
+            __builtin_amdgcn_sched_barrier(0);
+            auto one = [&](double p, double pxm2, double pxm, double pxp, double pxp2, double p_yp, double p_ym,
+                           double pzp, double pzm, double pzp2, double pzm2, double p_yp2, double p_ym2,
+                           double l_mu, double m, double l_g, double g) -> double {
+                double r = r0;
+                if constexpr (!BEND) {
+                    r += (3.0 * p * p - 1.0) * m - sigma * l_mu;
+                } else {
+                    const double lphi = (pxp + pxm + p_yp + p_ym + pzp + pzm - 6.0 * p) * d.inv_h2;
+                    const double gc = p * p * p - p - eps2 * lphi;
+                    r += 6.0 * C_b * p * gc * m - gam * l_mu + (3.0 * p * p - 1.0) * g - eps2 * l_g;
+                    if (area) {
+                        // dA/dphi = 3/(2 sqrt 2) h^3 [eps sum_c D_c^T (w D_c phi) + w (phi^2 - 1) phi / eps]
+                        const double dxm = (p - pxm2) * d.inv_2h, dxp = (pxp2 - p) * d.inv_2h;
+                        const double dzm = (p - pzm2) * d.inv_2h, dzp = (pzp2 - p) * d.inv_2h;
+                        double div = w * ((dxm - dxp) + (dzm - dzp));
+                        if (in_m) div += (p - p_ym2) * d.inv_2h;
+                        if (in_p) div -= (p_yp2 - p) * d.inv_2h;
+                        const double dA = 3.0 / (2.0 * 1.4142135623730951) * h3 *
+                                          (eps * div * d.inv_2h + w * (p * p - 1.0) * p / eps);
+                        r += Abar * dA;
+                    }
+                }
+                return r;
+            };
+            Pair8 r;
+            r.x = old.x + one(p0.x, pm2.x, pm1.x, pp1.x, pp2.x, pyp.x, pym.x, p0.y, pL.y, pR.x, pL.x, py2.x, pn2.x,
+                              lapt(mp.x, mm.x, m0.y, ml, myp.x, mym.x, m0.x), m0.x,
+                              lapt(gp.x, gm.x, g0.y, gl, gyp.x, gym.x, g0.x), g0.x);
+            r.y = old.y + one(p0.y, pm2.y, pm1.y, pp1.y, pp2.y, pyp.y, pym.y, pR.x, p0.x, pR.y, pL.y, py2.y, pn2.y,
+                              lapt(mp.y, mm.y, mr, m0.x, myp.y, mym.y, m0.y), m0.y,
+                              lapt(gp.y, gm.y, gr, g0.x, gyp.y, gym.y, g0.y), g0.y);
+            *out = r;
+            pm2 = pm1; pm1 = p0; p0 = pp1; pp1 = pp2;
+            mm = m0; m0 = mp;
+            gm = g0; g0 = gp;
+        }
+    };
+    if (ch) walk(std::false_type{});
+    else walk(std::true_type{});
 }
 
 }  // namespace
 
-// x-slabs of about 8 planes for the marching reverse kernels (at most 512 blocks)
-SlabGrid adj_slab_grid(const Dims& d) { return slab_grid(d.ny * d.nz, d.nx, 512); }
+// Blocks of k_adj_mu1 and k_adj_mu2, at most 512: longer walks re-read less, and every mu2 block adds
+// up mu1's partials (96^3, mu1 and mu2: 7.4 + 12.8, 6.6 + 11.6, 7.1 + 16.3, 7.7 + 21.0 us at up to 256,
+// 512, 1024, 2048 blocks)
+SlabGrid adj_slab_grid(const Dims& d) { return slab_grid(d.ny * (d.nz / 2), d.nx, 512); }
 
 void launch_adj_advect(hipStream_t s, const Dims& d, const double* a, const double* phi,
                        const double* const psi[3], double dt, double mobility, double vz_lo,

@@ -27,39 +27,7 @@ namespace {
 // even n_z), walking the ci x-planes of its block with the x neighbours held in registers. A
 // field's read of a pair moves 16 bytes; the z neighbours outside the pair are one 8-byte load
 // each. All loads of a plane are issued before the first use (scheduling barrier), so that one
-// latency is paid a plane. A lane's place in the plane:
-struct DiagLane {
-    int j, k;                // row, first z of the pair
-    int i0, i1;              // x-planes
-    int o, oyp, oym;         // offsets in a plane: the pair, its y neighbours (mirror ghosts)
-    int ol, orr;             // the nodes before and after the pair
-    int plane;
-    bool ok;
-};
-__device__ __forceinline__ DiagLane diag_lane(const Dims& d, const SlabGrid& sg) {
-    const int lb = xcd_block(blockIdx.x, sg.gx * sg.gi);
-    const int bi = lb / sg.gx;
-    const int hz = d.nz >> 1;
-    const int t = (lb - bi * sg.gx) * kBlock + threadIdx.x;
-    DiagLane L;
-    L.ok = t < d.ny * hz;
-    const int tc = L.ok ? t : 0;
-    L.j = tc / hz;
-    L.k = 2 * (tc - L.j * hz);
-    const int re = L.j * d.nz;
-    L.o = re + L.k;
-    L.oyp = ((L.j + 1 == d.ny) ? d.ny - 2 : L.j + 1) * d.nz + L.k;
-    L.oym = ((L.j == 0) ? 1 : L.j - 1) * d.nz + L.k;
-    L.ol = re + (L.k == 0 ? d.nz - 1 : L.k - 1);
-    L.orr = re + (L.k + 2 == d.nz ? 0 : L.k + 2);
-    L.plane = d.ny * d.nz;
-    L.i0 = bi * sg.ci;
-    L.i1 = min(d.nx, L.i0 + sg.ci);
-    return L;
-}
-__device__ __forceinline__ double2 ldp(const double* p) {
-    return *reinterpret_cast<const double2*>(p);
-}
+// latency is paid a plane.
 __device__ __forceinline__ double block_max(double v, double* sh) {   // in thread 0, fixed order
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -89,7 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_diag_flow(const double* __restrict__
     __shared__ double shm[16];
     double acc[3] = {0.0, 0.0, 0.0};
     double vmax = 0.0;
-    const DiagLane L = diag_lane(d, sg);
+    const PairLane L = pair_lane(d, sg);
     if (L.ok) {
         const double *__restrict__ px = vel.px, *__restrict__ py = vel.py, *__restrict__ pz = vel.pz;
         const double w = wrow(d, L.j);
@@ -171,7 +139,7 @@ __global__ __launch_bounds__(kBlock) void k_diag_shear(const double* __restrict_
     __shared__ double shm[16];
     double acc[1] = {0.0};
     double smax = 0.0;
-    const DiagLane L = diag_lane(d, sg);
+    const PairLane L = pair_lane(d, sg);
     if (L.ok) {
         const double w = wrow(d, L.j);
         const double eps2 = eps * eps;

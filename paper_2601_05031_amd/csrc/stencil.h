@@ -120,25 +120,40 @@ __device__ __forceinline__ double dcen(const double* __restrict__ u, const Dims&
 
 __device__ __forceinline__ bool interior(const Dims& d, int j) { return j >= 1 && j <= d.ny - 2; }
 
-// Walks a slab of x-planes per thread (the block-partial layout of the forward reductions).
-struct SlabIter {
-    int j, k, i0, i1;
+// A lane's place where a lane owns two consecutive z of a row (any even n_z) and its block walks
+// the x-planes [i0, i1), sg over the pairs of a plane.
+struct PairLane {
+    int j, k;                // row, first z of the pair
+    int i0, i1;              // x-planes
+    int o, oyp, oym;         // offsets in a plane: the pair, its y neighbours (mirror ghosts)
+    int ol, orr;             // the nodes before and after the pair
+    int plane;
     bool ok;
 };
-__device__ __forceinline__ SlabIter slab_iter(const Dims& d, const SlabGrid& sg) {
-    const int nb = sg.gx * sg.gi;
-    const int lb = xcd_block(blockIdx.x, nb);
+__device__ __forceinline__ PairLane pair_lane(const Dims& d, const SlabGrid& sg) {
+    const int lb = xcd_block(blockIdx.x, sg.gx * sg.gi);
     const int bi = lb / sg.gx;
+    const int hz = d.nz >> 1;
     const int t = (lb - bi * sg.gx) * kBlock + threadIdx.x;
-    SlabIter it;
-    it.ok = t < d.ny * d.nz;
-    it.j = it.ok ? t / d.nz : 0;
-    it.k = it.ok ? t - it.j * d.nz : 0;
-    it.i0 = bi * sg.ci;
-    it.i1 = min(d.nx, (bi + 1) * sg.ci);
-    return it;
+    PairLane L;
+    L.ok = t < d.ny * hz;
+    const int tc = L.ok ? t : 0;
+    L.j = tc / hz;
+    L.k = 2 * (tc - L.j * hz);
+    const int re = L.j * d.nz;
+    L.o = re + L.k;
+    L.oyp = ((L.j + 1 == d.ny) ? d.ny - 2 : L.j + 1) * d.nz + L.k;
+    L.oym = ((L.j == 0) ? 1 : L.j - 1) * d.nz + L.k;
+    L.ol = re + (L.k == 0 ? d.nz - 1 : L.k - 1);
+    L.orr = re + (L.k + 2 == d.nz ? 0 : L.k + 2);
+    L.plane = d.ny * d.nz;
+    L.i0 = bi * sg.ci;
+    L.i1 = min(d.nx, L.i0 + sg.ci);
+    return L;
 }
-
+__device__ __forceinline__ double2 ldp(const double* p) {
+    return *reinterpret_cast<const double2*>(p);
+}
 inline dim3 plane_grid(const Dims& d) {
     return dim3((unsigned)((d.ny * d.nz + kBlock - 1) / kBlock), (unsigned)d.nx, 1);
 }
