@@ -54,20 +54,29 @@ inline AdjTile adj_tile(const Dims& d) {
     t.tj = d.nz >= 512 ? 1 : 512 / d.nz;
     if (t.tj > d.ny) t.tj = d.ny;
     t.ntile = (d.ny + t.tj - 1) / t.tj;
-    // slabs of four planes, longer where the block partials would not fit
-    t.ci = 4;
+    // the shortest slabs, up to four planes, whose blocks run in one round (two a CU): each block is
+    // a serial walk, so short slabs win until a second round starts (advection and source at 1, 2, 4
+    // planes: 32^3 8.1 + 8.9, 11.4 + 11.6, 15.2 + 15.7 us; 64^3 12.4 + 10.9, 12.1 + 12.8, 16.8 +
+    // 17.5; 48 x 130 x 96 at 3 and 4 planes 19.1 + 17.5, 23.0 + 20.5; 96^3 at 2, 3, 4 and 8 planes 26.0 +
+    // 22.8, 27.7 + 24.5, 22.9 + 21.9, 26.6 + 30.4). Longer where the block partials would not fit
+    t.ci = 1;
+    while (t.ntile * ((d.nx + t.ci - 1) / t.ci) > 512 && t.ci < 4) ++t.ci;
     while (t.ntile * ((d.nx + t.ci - 1) / t.ci) > kMaxPartialBlocks && t.ci < d.nx) ++t.ci;
     t.nslab = (d.nx + t.ci - 1) / t.ci;
     return t;
 }
 
-// Tiles of the reverse node kernels: a block of kBlock lanes owns tj consecutive rows (all z)
+// Tiles of the reverse node kernels: a block of kAdjBlock lanes owns tj consecutive rows (all z)
 // of an x-slab of ci planes and walks the slab. Per plane, every quantity a node's outputs take
 // from its y and z neighbours is computed once per node of the tile and of its two halo rows and
 // exchanged through LDS; the x neighbours' come from registers kept from plane to plane. A lane
-// owns at most kAdjOwn nodes of the tile (tj nz <= kAdjOwn kBlock) and kAdjHalo halo nodes.
-constexpr int kAdjOwn = 2;
-constexpr int kAdjHalo = 4;
+// owns at most kAdjOwn nodes of the tile (tj nz <= kAdjOwn kAdjBlock) and kAdjHalo halo nodes.
+// Bound by latency: a plane is two phases of loads, a barrier and one of LDS reads in each block.
+// One node per lane (512 lanes) rather than two (256): half the chain, 106 and 90 registers for 177
+// and 151, so twice the waves; 96^3: advection 30.8 -> 22.9 us, source 28.8 -> 21.9.
+constexpr int kAdjBlock = 512;
+constexpr int kAdjOwn = 1;
+constexpr int kAdjHalo = 2;
 
 __device__ __forceinline__ void adj_tile_block(const Dims& d, const AdjTile& tl, int& j0, int& tjr,
                                                int& i0, int& i1) {
@@ -93,7 +102,7 @@ __device__ __forceinline__ void adj_tile_block(const Dims& d, const AdjTile& tl,
 struct AdjZero {
     double* p[6];
 };
-__global__ __launch_bounds__(kBlock) void k_adj_advect(
+__global__ __launch_bounds__(kAdjBlock) void k_adj_advect(
     const double* __restrict__ a, const double* __restrict__ phi, Vel vel, Dims d, double dt,
     double mob, AdjTile tl, double* __restrict__ phibar, double* __restrict__ mubar,
     double* __restrict__ qx, double* __restrict__ qy, double* __restrict__ qz,
@@ -120,7 +129,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_advect(
     double a0[kAdjOwn], ax0[kAdjOwn], by0[kAdjOwn], bz0[kAdjOwn];
 #pragma unroll
     for (int m = 0; m < kAdjOwn; ++m) {
-        const int idx = threadIdx.x + m * kBlock;
+        const int idx = threadIdx.x + m * kAdjBlock;
         ok[m] = idx < tjr * nz;
         const int r = ok[m] ? idx / nz : 0;
         oj[m] = j0 + r;
@@ -184,7 +193,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_advect(
         // halo rows j0 - 1 and j0 + tjr: a, A_y, b_x, b_z
 #pragma unroll 1
         for (int h = 0; h < kAdjHalo; ++h) {
-            const int idx = threadIdx.x + h * kBlock;
+            const int idx = threadIdx.x + h * kAdjBlock;
             if (idx >= 2 * nz) continue;
             const int side = idx / nz, k = idx - side * nz;
             const int j = side ? j0 + tjr : j0 - 1;
@@ -311,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_couple(const double* __rest
 // kAdjSlotOm: Sbar against the omega walls), and, when chk.part is given, block 0 first takes
 // the convergence check of the two adjoint solves from their residual partials (as
 // k_check_flow does; the slots of this kernel lie above the residual's).
-__global__ __launch_bounds__(kBlock) void k_adj_source(
+__global__ __launch_bounds__(kAdjBlock) void k_adj_source(
     const double* __restrict__ phi, const double* __restrict__ mu, const double* __restrict__ s0,
     const double* __restrict__ s1, const double* __restrict__ s2, Dims d, double inv_eta,
     AdjTile tl, double* __restrict__ phibar, double* __restrict__ mubar, WallPairs wp,
@@ -346,7 +355,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_source(
     int oj[kAdjOwn], ok_[kAdjOwn], orow[kAdjOwn];
 #pragma unroll
     for (int m = 0; m < kAdjOwn; ++m) {
-        const int idx = threadIdx.x + m * kBlock;
+        const int idx = threadIdx.x + m * kAdjBlock;
         ok[m] = idx < tjr * nz;
         const int r = ok[m] ? idx / nz : 0;
         oj[m] = j0 + r;
@@ -421,7 +430,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_source(
         // halo rows j0 - 1 and j0 + tjr: abar_y, bbar_y
 #pragma unroll 1
         for (int h = 0; h < kAdjHalo; ++h) {
-            const int idx = threadIdx.x + h * kBlock;
+            const int idx = threadIdx.x + h * kAdjBlock;
             if (idx >= 2 * nz) continue;
             const int side = idx / nz, k = idx - side * nz;
             const int j = side ? j0 + tjr : j0 - 1;
@@ -716,7 +725,7 @@ void launch_adj_advect(hipStream_t s, const Dims& d, const double* a, const doub
     AdjZero zw{};
     for (int f = 0; f < 6; ++f) zw.p[f] = zero_walls ? zero_walls[f] : nullptr;
     const size_t lds = (size_t)6 * (tl.tj + 2) * d.nz * sizeof(double);
-    launch_kernel(k_adj_advect, dim3(nb), dim3(kBlock), lds, s, a, phi, vel, d, dt, mobility, tl,
+    launch_kernel(k_adj_advect, dim3(nb), dim3(kAdjBlock), lds, s, a, phi, vel, d, dt, mobility, tl,
                   phibar, mubar, psibar[0], psibar[1], psibar[2], part, zw, scal, istat);
 }
 
@@ -746,7 +755,7 @@ void launch_adj_source(hipStream_t s, const Dims& d, const double* phi, const do
         wp.sw[c] = om_walls[c];
     }
     const size_t lds = (size_t)4 * (tl.tj + 2) * d.nz * sizeof(double);
-    launch_kernel(k_adj_source, dim3(tl.ntile * tl.nslab), dim3(kBlock), lds, s, phi, mu,
+    launch_kernel(k_adj_source, dim3(tl.ntile * tl.nslab), dim3(kAdjBlock), lds, s, phi, mu,
                   (const double*)sbar[0], (const double*)sbar[1], (const double*)sbar[2], d, inv_eta,
                   tl, phibar, mubar, wp, part, chk);
 }

@@ -1,5 +1,5 @@
 """The reverse step at the edges of its pair kernels: rows of an odd number of pairs and of few,
-walks with a short last slab, and adj_prev 8-byte but not 16-byte aligned, against the oracle."""
+walks with a short last slab, one row per tile, and adj_prev 8-byte but not 16-byte aligned, against the oracle."""
 import numpy as np
 import pytest
 
@@ -17,7 +17,7 @@ import paper_2601_05031_amd as P  # noqa: E402
 
 
 @pytest.mark.parametrize("model", ["bending", "cahn_hilliard"])
-@pytest.mark.parametrize("shape", [(16, 9, 4), (12, 8, 18), (54, 40, 6), (36, 70, 108), (96, 40, 64)])
+@pytest.mark.parametrize("shape", [(16, 9, 4), (12, 8, 18), (54, 40, 6), (36, 70, 108), (96, 40, 64), (6, 7, 512)])
 def test_pairs(shape, model):
     print(f"case grad-step {shape} {model}", flush=True)
     nx, ny, nz = shape
