@@ -449,15 +449,21 @@ __global__ __launch_bounds__(64) void k_rhs_hz(Dims d, const double2* __restrict
             const int k = k1 + A * k2;
             return mkc<T>((T)(sg * fc[max(o.x, 0) + k]), (T)(sg * fc[max(o.y, 0) + k]));
         };
+        // f minus the wall terms of a row's flags, in FP64 and rounded to T once: f is read again where
+        // the loaded value was rounded already (near the walls f and wall / h^2 may nearly cancel)
+        auto wall_row = [&](T v, int o, int fl, int k) -> T {
+            double b = sizeof(T) == 8 ? (double)v : sg * fc[o + k];
+            if (fl & 1) b -= uc[o - d.nz + k] * d.inv_h2;
+            if (fl & 2) b -= uc[o + d.nz + k] * d.inv_h2;
+            return (T)b;
+        };
         auto walls = [&](const int4& o, int k1, C* x) {
             if (!(o.z | o.w)) return;
 #pragma unroll
             for (int k2 = 0; k2 < B; ++k2) {
                 const int k = k1 + A * k2;
-                if (o.z & 1) x[k2].x = (T)((double)x[k2].x - uc[o.x - d.nz + k] * d.inv_h2);
-                if (o.z & 2) x[k2].x = (T)((double)x[k2].x - uc[o.x + d.nz + k] * d.inv_h2);
-                if (o.w & 1) x[k2].y = (T)((double)x[k2].y - uc[o.y - d.nz + k] * d.inv_h2);
-                if (o.w & 2) x[k2].y = (T)((double)x[k2].y - uc[o.y + d.nz + k] * d.inv_h2);
+                if (o.z) x[k2].x = wall_row(x[k2].x, o.x, o.z, k);
+                if (o.w) x[k2].y = wall_row(x[k2].y, o.y, o.w, k);
             }
         };
         auto storew = [&](const int4& o, int p, T ha, T hb) {
