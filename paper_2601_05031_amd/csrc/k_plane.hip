@@ -132,7 +132,8 @@ struct PlaneShape {
 // would not fit in the registers). The twiddles sit in LDS, so no global load inside the
 // transforms waits behind the prefetch.
 // RHS (with ZFIRST): the right-hand side of a direct solve, z.sgn times the field minus the wall
-// terms, which the planes j = 1 and j = M take from the wall rows of z.wall.
+// terms, which the planes j = 1 and j = M take from the wall rows of z.wall. Its field and walls, and
+// z.u, may be the caller's arrays: 8-byte aligned.
 template <int BX, int AX, int BZ, int AZ, bool ZFIRST, bool BATCH, bool RHS = false>
 __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, AX, BZ, AZ>::WPE)) void k_hxz_plane(
     Dims d, int nc, ZArgs zone, const ZArgs* __restrict__ ztab, HxArgs xone,
@@ -194,7 +195,7 @@ __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, A
             if (r < r0 || r >= r1) continue;
             const int t = min((int)threadIdx.x + r * NT, NV - 1);
             const int i = t / (NZ / 2), k2 = t - i * (NZ / 2);
-            v[r] = ldg2(in + i * pstride + 2 * k2);
+            v[r] = RHS ? ldg2u(in + i * pstride + 2 * k2) : ldg2(in + i * pstride + 2 * k2);
         }
         if constexpr (RHS) {
             const int cg = p / d.M, j = 1 + (p - cg * d.M);
@@ -210,12 +211,12 @@ __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, A
                 const int i = t / (NZ / 2), k2 = t - i * (NZ / 2);
                 const Gl<double>* w = (const Gl<double>*)pick(zone.wall, cg) + i * pstride + 2 * k2;
                 if (j == 1) {
-                    const double2 u = ldg2(w);
+                    const double2 u = ldg2u(w);
                     v[r].x -= u.x * d.inv_h2;
                     v[r].y -= u.y * d.inv_h2;
                 }
                 if (j == d.M) {
-                    const double2 u = ldg2(w + (size_t)(d.ny - 1) * NZ);
+                    const double2 u = ldg2u(w + (size_t)(d.ny - 1) * NZ);
                     v[r].x -= u.x * d.inv_h2;
                     v[r].y -= u.y * d.inv_h2;
                 }
@@ -259,7 +260,7 @@ __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, A
             if (t < NV) {
                 const int i = t / (NZ / 2), k2 = t - i * (NZ / 2);
                 const double2 w = *reinterpret_cast<const double2*>(&P[i * RS + 2 * k2]);
-                stc<double>(out + i * pstride + 2 * k2, w.x, w.y);
+                stg2u(out + i * pstride + 2 * k2, w.x, w.y);
             }
         }
         __syncthreads();   // the plane's LDS is read out before the next one is written

@@ -118,7 +118,7 @@ __device__ __forceinline__ void any_pass(int n, double* __restrict__ P, int RS, 
 
 // As k_hxz_plane (ZFIRST: z then x from z.spec into x.spec, with z.wall the right-hand side of a
 // direct solve; otherwise x then z from x.spec into z.u; gated per instance by z.gate). LDSD: doubles
-// of LDS, WPE: waves per SIMD the registers are held to.
+// of LDS, WPE: waves per SIMD the registers are held to. Loads and stores need 8-byte alignment only.
 template <int LDSD, int NT, int WPE, bool ZFIRST, bool BATCH>
 __global__ __launch_bounds__(NT, WPE) void k_plane_any(Dims d, int nc, PlaneAny pa, ZArgs zone,
                                                        const ZArgs* __restrict__ ztab, HxArgs xone,
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(NT, WPE) void k_plane_any(Dims d, int nc, PlaneAny 
         for (int i0 = wv * pa.rpw; i0 < nx; i0 += U * stride) {
             double2 v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = ldg2(in + min(i0 + r + u * stride, nx - 1) * pstride + kc);
+            for (int u = 0; u < U; ++u) v[u] = ldg2u(in + min(i0 + r + u * stride, nx - 1) * pstride + kc);
             if (ZFIRST && !BATCH && za.wall[0]) {
                 const Gl<double>* w = (const Gl<double>*)pick(za.wall, c) + kc;
 #pragma unroll
@@ -162,12 +162,12 @@ __global__ __launch_bounds__(NT, WPE) void k_plane_any(Dims d, int nc, PlaneAny 
                     v[u].x *= za.sgn;
                     v[u].y *= za.sgn;
                     if (j == 1) {
-                        const double2 q = ldg2(wi);
+                        const double2 q = ldg2u(wi);
                         v[u].x -= q.x * d.inv_h2;
                         v[u].y -= q.y * d.inv_h2;
                     }
                     if (j == d.M) {
-                        const double2 q = ldg2(wi + (size_t)(d.ny - 1) * nz);
+                        const double2 q = ldg2u(wi + (size_t)(d.ny - 1) * nz);
                         v[u].x -= q.x * d.inv_h2;
                         v[u].y -= q.y * d.inv_h2;
                     }
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(NT, WPE) void k_plane_any(Dims d, int nc, PlaneAny 
                 const int i = i0 + r + u * stride;
                 if (ok && i < nx) {
                     const double2 q = *reinterpret_cast<const double2*>(&P[i * RS + kc]);
-                    stc<double>(out + i * pstride + kc, q.x, q.y);
+                    stg2u(out + i * pstride + kc, q.x, q.y);
                 }
             }
         }

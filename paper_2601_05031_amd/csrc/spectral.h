@@ -139,6 +139,20 @@ __device__ __forceinline__ double2 ldg2(const Gl<float>* p) {
     return make_double2((double)v.x, (double)v.y);
 }
 
+// The same for arrays of the caller's, which need be aligned as doubles only (include/vs.h); one 16-byte
+// access either way (the target takes unaligned vectors).
+typedef double gd2u __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ double2 ldg2u(const Gl<double>* p) {
+    const gd2u v = *reinterpret_cast<const Gl<gd2u>*>(p);
+    return make_double2(v.x, v.y);
+}
+__device__ __forceinline__ void stg2u(Gl<double>* p, double a, double b) {
+    gd2u v;
+    v.x = a;
+    v.y = b;
+    *reinterpret_cast<Gl<gd2u>*>(p) = v;
+}
+
 // The instance of a block and its index inside the instance: logical blocks are split into
 // runs of nb per instance (see Over in vs_internal.h).
 // A reference, not a copy: the structs hold small pointer arrays indexed by the block's

@@ -1,5 +1,5 @@
 """Poisson solves of inputs at the edges of what the direct cycle accepts: right-hand sides that
-nearly cancel against the wall terms."""
+nearly cancel against the wall terms, and arrays that are aligned as doubles only."""
 import numpy as np
 import pytest
 
@@ -50,3 +50,38 @@ def test_wall_terms_are_subtracted_before_the_refined_cycle_rounds(shape):
     e = rel_l2(got[:, 1:-1], O.poisson_solve(rhs, zero, zero, O.Grid(*shape)))
     print(f"  relL2={e:.2e} relres={rel:.2e}", flush=True)
     assert e <= 1e-4, e
+
+
+def odd_view(a):
+    """A copy of a at 8 bytes past a 16-byte boundary, inside guard values."""
+    flat = torch.full((a.numel() + 3,), 7.0, dtype=torch.float64, device="cuda")
+    first = 1 if flat.data_ptr() % 16 == 0 else 2
+    v = flat[first:first + a.numel()].view(a.shape)
+    v.copy_(a)
+    assert v.data_ptr() % 16 == 8
+    return flat, first, v
+
+
+# planes with a kernel of their own, alone and several on a CU, planes of the shared kernel (both sizes),
+# and line passes
+@pytest.mark.parametrize("shape", [(128, 5, 128), (48, 7, 32), (24, 6, 36), (72, 3, 108), (192, 5, 64), (18, 6, 16)])
+@pytest.mark.parametrize("entry", ["state", "noalloc"])
+def test_arrays_aligned_as_doubles_only(shape, entry):
+    print(f"case poisson alignment {entry} {shape}", flush=True)
+    rng = np.random.default_rng(7)
+    f, u = (torch.tensor(rng.standard_normal(shape), device="cuda") for _ in range(2))
+    if entry == "state":
+        s = P.solver_for(workload("droplet256", grid=GridSpec(*shape), R0=1.0, max_cycles=3))
+        solve = s.poisson_solve
+    else:
+        solve = V.poisson_solve_noalloc
+    ref = u.clone()
+    assert solve(f, ref, rtol=1e-12, max_cycles=2)[:2] == (V.VS_OK, 1)
+    ff, f0, fo = odd_view(f)
+    uf, u0, uo = odd_view(u)
+    assert solve(fo, uo, rtol=1e-12, max_cycles=2)[:2] == (V.VS_OK, 1)
+    if entry == "state":
+        s.close()
+    assert torch.equal(uo, ref) and torch.equal(fo, f)
+    for flat, first in ((ff, f0), (uf, u0)):
+        assert (flat[:first] == 7.0).all() and (flat[first + f.numel():] == 7.0).all()
