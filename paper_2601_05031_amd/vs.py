@@ -389,10 +389,18 @@ def rollout_gradient(solver: "Solver", dt: float, nsteps: int, target, checkpoin
     torch = solver.torch
     ce = max(1, int(checkpoint_every))
     ckpt = {0: solver.save(device=True)}   # checkpoints stay in HBM
-    for n in range(0, nsteps, ce):
-        solver.step(dt, min(ce, nsteps - n))
-        if n + ce <= nsteps:
-            ckpt[n + ce] = solver.save(device=True)
+    # vs_step tests dt against the forward-Euler bound once, with the gamma_A it finds: a segment is one
+    # call only where the bound cannot move inside it, else every step is a call of its own
+    p = solver.params
+    fixed = (p.model == VS_CAHN_HILLIARD or p.flags & VS_ALLOW_UNSTABLE
+             or p.k_A == 0.0 and solver.scalars()["gamma_A"] == p.gamma0)
+    n = 0
+    while n < nsteps:
+        k = min(ce, nsteps - n) if fixed else 1
+        solver.step(dt, k)
+        n += k
+        if n % ce == 0:
+            ckpt[n] = solver.save(device=True)
     r = solver.field("phi") - target
     loss = float((r * r).sum())
     a = (2.0 * r).contiguous()
