@@ -15,8 +15,8 @@ namespace {
 // and one component sits in LDS (n_x (n_z + 2) doubles, 133 KB at 128 x 128), so the spectral
 // data crosses HBM once per direction instead of twice. Each 1D
 // transform is the two-pass form above done in place in the plane: pass 1 overwrites the B
-// inputs of its (line pair, k1) with their twiddled B-point DFT, pass 2 reads the A values of
-// rows pa, pb, and after a barrier writes the Hartley values. z lines are pairs of x-rows
+// inputs of its (line pair, k1), or with the swizzle below those of its line pair, with their twiddled
+// B-point DFT, pass 2 reads the A values of rows pa, pb, and after a barrier writes the Hartley values. z lines are pairs of x-rows
 // (i, i+1), x lines pairs of z-columns (q, q+1) as in k_hx.
 // Padded row of the plane for z lines of shape (B, A): the 2 A (FP64) or A (FP32) dwords that A
 // lanes of a line pair read land next to those of the following pairs, in other banks.
@@ -48,8 +48,10 @@ __device__ __forceinline__ void plane_hartley(T* __restrict__ P, const tw2v* __r
     };
     // z lines with A a power of two hold their pass-1 result k1 of row p2 at A p2 + (k1 ^ p2 mod A):
     // in place of k1 + A p2, where the B/2 lanes of a line pair would read pass 2 in a stride of
-    // A, on a few banks
+    // A, on a few banks. A lane then overwrites inputs of the line pair's other lanes: all A of them
+    // are in one wave, which issues its loads before its stores (swizzle_order)
     constexpr int SW = ROWS && (A & (A - 1)) == 0 ? A - 1 : 0;
+    static_assert(SW == 0 || 64 % A == 0, "the lanes of a swizzled line pair share a wave");
     // pass 1: B-point DFTs over k2, twiddled, back to the same positions k1 + A p2
     if (it < NLP * A) {
         const int lp = ROWS ? it / A : it % NLP;
@@ -60,6 +62,7 @@ __device__ __forceinline__ void plane_hartley(T* __restrict__ P, const tw2v* __r
         fftr::DFT<B>::run(x);
 #pragma unroll
         for (int p2 = 1; p2 < B; ++p2) x[p2] = cmul_tw<T>(x[p2], tw[k1 * p2]);
+        if constexpr (SW != 0) swizzle_order();
 #pragma unroll
         for (int p2 = 0; p2 < B; ++p2) st(lp, (k1 ^ (p2 & SW)) + A * p2, x[p2].x, x[p2].y);
     }

@@ -31,6 +31,7 @@ __device__ __forceinline__ void any_hartley(double* __restrict__ P, int RS, int 
     using C = double2;
     constexpr int IT = A > B / 2 ? A : B / 2, LPR = NT / IT;
     constexpr int SW = ROWS && (A & (A - 1)) == 0 ? A - 1 : 0;   // LDS bank spread, see k_plane.hip
+    static_assert(SW == 0 || 64 % A == 0, "the lanes of a swizzled line pair share a wave");
     auto ld = [&](int lp, int m) -> C {
         if constexpr (ROWS) return make_double2(P[(2 * lp) * RS + m], P[(2 * lp + 1) * RS + m]);
         else return *reinterpret_cast<const C*>(&P[m * RS + 2 * lp]);
@@ -60,6 +61,7 @@ __device__ __forceinline__ void any_hartley(double* __restrict__ P, int RS, int 
                 fftr::DFT<B>::run(x);
 #pragma unroll
                 for (int p2 = 1; p2 < B; ++p2) x[p2] = cmul_tw<double>(x[p2], tw[k1 * p2]);
+                if constexpr (SW != 0) swizzle_order();
 #pragma unroll
                 for (int p2 = 0; p2 < B; ++p2) st(lp, (k1 ^ (p2 & SW)) + A * p2, x[p2].x, x[p2].y);
             }

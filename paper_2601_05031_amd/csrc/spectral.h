@@ -93,6 +93,14 @@ __device__ __forceinline__ T ldt(const double* p) { return (T)*p; }
 template <class T>
 __device__ __forceinline__ T ldt(const float* p) { return (T)*p; }
 
+// Orders a wave's LDS loads before the stores that follow where its lanes overwrite each other's inputs
+// (the plane transforms' swizzle): the hardware keeps a wave's LDS accesses in order, the compiler
+// must not move them across.
+__device__ __forceinline__ void swizzle_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Objects in global memory. Pointers that a batched launch reads from its device table are
 // generic; typing the accesses through them as global keeps them global loads and stores
 // (flat ones would also count against the LDS counter). Pairs go through clang's vector
