@@ -250,6 +250,9 @@ struct vs_state {
     long long step = 0;
     double last_relres = 0.0;
     int last_cycles = 0;
+    // FP64, poisson_max_cycles > 1: most steps of the last call, or the last reverse step, needed
+    // correction cycles, so the next one enqueues them in line (see halting)
+    bool corr_steps = false, corr_grad = false;
     // event timer
     bool prof_on = false;
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> ev_used;
@@ -791,7 +794,11 @@ bool enqueue_flow_args(const StepCfg& c, const StepArgs& A, bool defer, int max_
 // The steps of a call run as those of max_cycles = 1, every kernel gated on IS_HALT; a check
 // that misses rtol sets it, so the state stays as that step's direct pass left it, and the
 // host, at the call's end, takes that step's corrections (enqueue_fp64_corrections) and the
-// remaining steps of the call with their corrections in line (collect).
+// remaining steps of the call with their corrections in line (collect). Where rtol is below what
+// the direct pass reaches, every call would pay for its gated launches and one more wait (ten steps
+// at 32^3: 1760 us against 1380); after a call of which most steps were corrected the next one takes
+// the corrections in line from its first step. Either way each step runs the same kernels on its
+// fields, so these do not depend on the choice.
 bool halting(const vs_state* S) { return !S->f32 && S->p.poisson_max_cycles > 1; }
 
 // Correction cycles after the direct pass, per solve, through the general verified path.
@@ -833,7 +840,7 @@ void enqueue_init(vs_state* S) {
 // One time step. first: of its call (it clears the status words). more_follow: another step of the
 // same call comes after this one, so its advance kernel can take this step's flow check; otherwise
 // the check writes the host copy of the status. inline_corr: FP64 correction cycles enqueued
-// with the step (the steps after a halt).
+// with the step (the steps after a halt, and calls that expect one).
 void enqueue_step(vs_state* S, double dt, bool first, bool more_follow, bool inline_corr = false) {
     const StepCfg c = step_cfg(S);
     const bool halt = halting(S) && !inline_corr;
@@ -920,11 +927,11 @@ vs_status read_status(vs_state* S, double* sc, int* ist, bool written = false) {
 // Waits for a call that enqueued nsteps steps of dt from phi[cur0] (nsteps = 0: the initial
 // solve) and maps the device flags to a status. Where a check halted the call at step k, the
 // fields are those of step k's direct pass: its correction cycles are taken first, then steps
-// k+1 .. nsteps with theirs in line.
-vs_status collect(vs_state* S, const char* what, double dt, int nsteps, int cur0) {
+// k+1 .. nsteps with theirs in line. inline_corr: all steps were enqueued with theirs.
+vs_status collect(vs_state* S, const char* what, double dt, int nsteps, int cur0, bool inline_corr = false) {
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
-    vs_status rs = read_status(S, sc, ist, true);
+    vs_status rs = read_status(S, sc, ist, !inline_corr);
     if (rs == VS_OK && ist[IS_HALT]) {
         const int k = nsteps ? ist[IS_PASSED] + 1 : 0;
         S->cur = (cur0 + k) & 1;
@@ -937,6 +944,8 @@ vs_status collect(vs_state* S, const char* what, double dt, int nsteps, int cur0
     S->gamma_host = sc[SC_GAMMA];
     S->last_relres = sc[SC_RELRES_MAX];
     S->last_cycles = ist[IS_CYCLES];
+    const int ns = nsteps ? nsteps : 1;   // two cycles a step, and at least one more if corrected
+    S->corr_steps = halting(S) && 2 * (ist[IS_CYCLES] - 2 * ns) > ns;
     if (ist[IS_FLAGS] & ST_NONFINITE)
         return fail(VS_E_NONFINITE, "%s: non-finite value in a residual norm or in V, A", what);
     if (ist[IS_FLAGS] & ST_NOCONV)
@@ -1324,10 +1333,11 @@ vs_status vs_step(vs_state* S, double dt, int32_t nsteps) {
     vs_status st = ensure_inertial_table(S, dt);
     if (st != VS_OK) return st;
     const int cur0 = S->cur;
-    for (int s = 0; s < nsteps; ++s) enqueue_step(S, dt, s == 0, s + 1 < nsteps);
+    const bool inl = S->corr_steps;
+    for (int s = 0; s < nsteps; ++s) enqueue_step(S, dt, s == 0, s + 1 < nsteps, inl);
     HIP_TRY(hipGetLastError());
     S->step += nsteps;
-    const vs_status cs = collect(S, "vs_step", dt, nsteps, cur0);
+    const vs_status cs = collect(S, "vs_step", dt, nsteps, cur0, inl);
     print_log(S);
     return cs;
 }
@@ -1465,17 +1475,26 @@ vs_status vs_grad_step(vs_state* S, double dt, const double* adj_next, double* a
     if (S->p.rho > 0.0)
         return fail(VS_E_UNSUPPORTED, "vs_grad_step: no reverse step for the inertial variant");
     const double rtol = S->p.poisson_rtol;
-    enqueue_grad(S, dt, adj_next, adj_prev, true);
-    HIP_TRY(hipGetLastError());
     int ist[IS_NSTAT];
     double sc[SC_NSCAL];
-    vs_status rs = read_status(S, sc, ist, true);
-    if (rs == VS_OK && (ist[IS_FLAGS] & ST_NOCONV) && S->p.poisson_max_cycles > 1) {
-        // the one pass missed rtol: the whole reverse step again (its inputs are untouched) with
-        // the correction cycles
-        enqueue_grad(S, dt, adj_next, adj_prev, false);
+    auto run = [&](bool one_pass) -> vs_status {
+        enqueue_grad(S, dt, adj_next, adj_prev, one_pass);
         HIP_TRY(hipGetLastError());
-        rs = read_status(S, sc, ist, true);
+        return read_status(S, sc, ist, true);
+    };
+    // One pass first; if it misses rtol, the whole reverse step again (its inputs are untouched) with
+    // the correction cycles. After a reverse step that took some, those come first (32^3 reverse step
+    // below the one pass's residual: 298 us against 243), and the one pass only if no solve needed
+    // them: the results stay those of the one pass wherever it meets rtol.
+    const bool corr = S->corr_grad;
+    vs_status rs = run(!corr);
+    if (rs == VS_OK && corr) {
+        S->corr_grad = ist[IS_CYCLES] > 2;
+        if (!S->corr_grad) rs = run(true);
+    }
+    if (rs == VS_OK && !S->corr_grad && (ist[IS_FLAGS] & ST_NOCONV) && S->p.poisson_max_cycles > 1) {
+        rs = run(false);
+        S->corr_grad = rs == VS_OK && ist[IS_CYCLES] > 2;
     }
     if (rs != VS_OK) return rs;
     if (ist[IS_FLAGS] & ST_NONFINITE) return fail(VS_E_NONFINITE, "vs_grad_step: non-finite residual");
@@ -2104,6 +2123,18 @@ vs_status batch_capture(vs_batch* B, const double* dt) {
     return VS_OK;
 }
 
+// Statuses of a batch's instances after nsteps (an even number) steps; the first failing one's.
+vs_status batch_collect(vs_batch* B, const double* dt, int nsteps, bool inline_corr) {
+    vs_status worst = VS_OK;
+    for (size_t i = 0; i < B->st.size(); ++i) {
+        vs_state* S = B->st[i];
+        S->step += nsteps;
+        const vs_status st = collect(S, "vs_batch_step", dt[i], nsteps, S->cur, inline_corr);
+        if (st != VS_OK && worst == VS_OK) worst = st;
+    }
+    return worst;
+}
+
 }  // namespace
 
 extern "C" {
@@ -2212,6 +2243,16 @@ vs_status vs_batch_step(vs_batch* B, const double* dt, int32_t nsteps) {
         const vs_status st = ensure_inertial_table(B->st[i], dt[i]);
         if (st != VS_OK) return st;
     }
+    // every instance expects to take its corrections in line: no graph (see halting)
+    bool inl = true;
+    for (const vs_state* S : B->st) inl = inl && S->corr_steps;
+    if (inl) {
+        HIP_TRY(hipStreamSynchronize(B->origin));
+        for (size_t i = 0; i < n; ++i)
+            for (int s = 0; s < nsteps; ++s) enqueue_step(B->st[i], dt[i], s == 0, s + 1 < nsteps, true);
+        HIP_TRY(hipGetLastError());
+        return batch_collect(B, dt, nsteps, true);
+    }
     bool same = B->exec && B->dt.size() == n && B->gen.size() == n;
     for (size_t i = 0; same && i < n; ++i) same = B->dt[i] == dt[i] && B->gen[i] == B->st[i]->walls_gen;
     if (!same) {
@@ -2222,14 +2263,7 @@ vs_status vs_batch_step(vs_batch* B, const double* dt, int32_t nsteps) {
     HIP_TRY(hipGetLastError());
     for (int r = 0; r < nsteps / 2; ++r) HIP_TRY(hipGraphLaunch(B->exec, B->origin));
     HIP_TRY(hipStreamSynchronize(B->origin));
-    vs_status worst = VS_OK;
-    for (size_t i = 0; i < n; ++i) {
-        vs_state* S = B->st[i];
-        S->step += nsteps;
-        const vs_status st = collect(S, "vs_batch_step", dt[i], nsteps, S->cur);
-        if (st != VS_OK && worst == VS_OK) worst = st;
-    }
-    return worst;
+    return batch_collect(B, dt, nsteps, false);
 }
 
 void vs_batch_destroy(vs_batch* B) {
