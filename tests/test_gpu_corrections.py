@@ -1,11 +1,14 @@
-"""FP64 with rtol below what the direct passes reach: every step and every reverse step takes correction
+"""FP64 with rtol at or below what the direct passes reach: steps and reverse steps that take correction
 cycles. After the first of them these are enqueued with the steps, not after a miss, and the direct
-form comes back once nothing needed them."""
+form comes back once nothing needed them. Each test asserts from launch counts or the log that the
+path it names has run: the separate residual passes, the general reverse step, halted instances."""
 import struct
 
 import numpy as np
 import pytest
 
+import oracle as O
+from oracle import adjoint as AD
 from workloads import workload
 from workloads.shapes import GridSpec
 
@@ -32,6 +35,12 @@ def rel_l2(a, b):
 def case(shape, seed=1, **kw):
     kw = dict(dict(rate_V=10.0, k_A=1.0, dt=5e-4, max_cycles=1), **kw)
     return workload("vesicle32", grid=GridSpec(*shape), R0=min(shape) / 4.0, seed=seed, **kw)
+
+
+def oracle_objs(w):
+    return (O.Grid(*w.grid.shape, h=w.grid.h), O.Walls(w.wall_kind, w.u0, w.u1),
+            O.Params(model=w.model, eta=w.eta, mobility=w.mobility, eps=w.eps, kappa=w.kappa, sigma=w.sigma,
+                     gamma0=w.gamma0, rate_V=w.rate_V, k_A=w.k_A, bend_scale=w.bend_scale))
 
 
 def allow_noconv(call):
@@ -158,3 +167,102 @@ def test_reverse_steps_that_miss_take_the_corrections_first(shape):
     assert rel_l2((b[1] - a).cpu().numpy(), (b[0] - a).cpu().numpy()) <= TOL
     for x in d:
         assert x == d[0] and x == pytest.approx(plain, rel=1e-9, abs=1e-18)
+
+
+# one cycle a solve leaves the general path only to correct: the reference is the oracle, at the bar of the
+# reverse step
+@pytest.mark.parametrize("name", ["vesicle32", "droplet256"])
+@pytest.mark.parametrize("shape", [(32, 21, 32), (32, 8, 48), (24, 13, 36), (18, 9, 24), (16, 6, 36)])
+def test_the_general_reverse_step_matches_the_oracle(shape, name):
+    w = workload(name, grid=GridSpec(*shape), R0=min(shape) / 4.0, wall_kind="couette", u0=-0.03, u1=0.05, rate_V=2.0,
+                 k_A=0.7 if name == "vesicle32" else 0.0, max_cycles=1)
+    an = np.random.default_rng(4).standard_normal(shape)
+    a = torch.tensor(an, device="cuda")
+    b = torch.empty_like(a)
+    s = P.solver_for(w)
+    s.grad_step(w.dt, a, b)
+    rtol = 0.98 * min(adjoint_residual(s), s.scalars()["relres"])
+    s.close()
+    s = P.solver_for(w.with_(max_cycles=16, rtol=rtol))
+    d = []
+    n = launches(s, lambda: d.append(s.grad_step(w.dt, a, b)))
+    s.close()
+    print(f"case general reverse {name} {shape} rtol={rtol:.2e} terms={d}", flush=True)
+    assert n["adj_wall_couple"] == 1 and n["tridiag_y"] > 2, n
+    g, walls, p = oracle_objs(w)
+    prev, kappa, scale = AD.grad_step(O.init_state(g, walls, p, w.phi0()), an, w.dt, g, walls, p)
+    assert np.linalg.norm(b.cpu().numpy() - prev) <= 1e-9 * np.linalg.norm(prev - an)
+    # at 32 x 21 x 32 no cycle need reach this rtol: VS_E_NOCONV, adj_prev written, no terms
+    assert len(d) == 1 or shape == (32, 21, 32)
+    for dk, ds in d:
+        assert dk == pytest.approx(kappa if name == "vesicle32" else 0.0, rel=1e-9, abs=1e-15)
+        assert ds == pytest.approx(scale, rel=1e-9, abs=1e-15)
+
+
+# the combined pass in its forms by n_z, and the separate passes of the same fields: a state made with a
+# right-hand side that missed takes its next call's steps in line, here from another state's checkpoint
+@pytest.mark.parametrize("shape", [(32, 32, 32), (16, 24, 48), (16, 24, 24), (16, 24, 64), (16, 24, 128), (12, 20, 256)])
+def test_separate_residual_passes_match_the_combined_one(shape):
+    runs = []
+    for seed in range(6):
+        s = P.solver_for(case(shape, seed))
+        blob = s.save()
+        s.step(5e-4, 3)
+        runs.append((s.log()[:, L["relres"]], blob, s.fields()))
+        s.close()
+    bad = max(range(6), key=lambda q: runs[q][0][0])
+    r, blob, ref = min(runs, key=lambda q: q[0].max())
+    assert runs[bad][0][0] > r.max() * (1.0 + 1e-9)
+    rtol = 0.5 * (runs[bad][0][0] + float(r.max()))
+    s = P.solver_for(case(shape, bad).with_(max_cycles=8, rtol=rtol))
+    s.load(blob)
+    n = launches(s, lambda: s.step(5e-4, 3))
+    got, log = s.fields(), s.log()
+    s.close()
+    print(f"case separate residuals {shape} combined {r[1:]} separate {log[-3:, L['relres']]}", flush=True)
+    assert (n["resid_norm_flow"], n["advance"]) == (0, 3) and list(log[-3:, L["cycles"]]) == [2, 4, 6]
+    for k in FIELD_NAMES:
+        assert np.array_equal(got[k], ref[k]), k
+    # the same residual terms, added in another order
+    assert log[-3:, L["relres"]] == pytest.approx(r[1:], rel=1e-12)
+
+
+# batched launches over a halted instance: the plane kernels of their own and the shared one, and the
+# register-marching mu, exit for it alone
+@pytest.mark.parametrize("shape", [(32, 21, 32), (64, 13, 48), (24, 17, 36), (16, 18, 72)])
+def test_a_batch_with_a_halted_instance_on_plane_grids(shape):
+    nsteps = 8
+    V.set_launch_shapes(shape + (1.0,), dict(adv_slab=4, va_maxb=1024, res_maxb=1024, seg_alt=0, mu_kind=2, mu_ni=2,
+                                             plane=1))
+    runs, halted = [], None
+    for seed in range(24):
+        w = case(shape, seed)
+        ref, r = uncorrected(w, nsteps)
+        up = [k for k in range(2, nsteps) if r[k] > r[:k].max() * (1.0 + 1e-9)]
+        if up and halted is None:
+            halted = up[0]
+            runs.append((w, ref, 0.5 * (float(r[:halted].max()) + r[halted]), halted))
+        elif len(runs) - (halted is not None) < 2:
+            runs.append((w, ref, 1e-10, None))
+        if halted is not None and len(runs) == 3:
+            break
+    assert halted is not None and len(runs) == 3
+    print(f"case halted in a batch {shape} seeds={[r[0].seed for r in runs]} k={[r[3] for r in runs]}", flush=True)
+    solvers = [P.solver_for(w.with_(max_cycles=3, rtol=rtol)) for w, _, rtol, _ in runs]
+    b = V.Batch(solvers, nstreams=2)
+    allow_noconv(lambda: b.step([w.dt for w, *_ in runs], nsteps))
+    b.close()
+    for s, (w, ref, rtol, k) in zip(solvers, runs):
+        got, log, sc = s.fields(), s.log(), s.scalars()
+        s.close()
+        assert sc["step"] == nsteps and list(log[:, L["index"]]) == list(range(nsteps + 1))
+        cyc = list(log[1:, L["cycles"]])
+        even = [2 * (q + 1) for q in range(nsteps)]
+        if k is None:
+            assert cyc == even
+            for q in FIELD_NAMES:
+                assert np.array_equal(got[q], ref[q]), q
+        else:
+            assert cyc[:k - 1] == even[:k - 1] and cyc[k - 1] > 2 * k
+            errs = {q: rel_l2(got[q], ref[q]) for q in FIELD_NAMES}
+            assert max(errs.values()) <= TOL, errs
