@@ -135,7 +135,8 @@ typedef struct {
  *  poisson_rtol, poisson_max_cycles: each Poisson solve of vs_step runs up to max_cycles
  *            refinement cycles until ||b - L_h u||_2 <= rtol ||b||_2 over the three
  *            components (b includes the wall terms); max_cycles in [1, 16]. In VS_FP64 the
- *            first cycle solves directly; later cycles are enqueued only after a check missed.
+ *            first cycle solves directly; later cycles are enqueued only after a check missed
+ *            (or with the steps, after a call of which most steps needed them).
  *  flags     VS_ALLOW_UNSTABLE skips the forward-Euler stability check of vs_step.
  *  rho       fluid density of the inertial variant (SM "Time-dependency and inertial flow",
  *            eq. (36)): (rho/eta) d(omega)/dt - lap omega = -(1/eta) grad phi x grad mu,
@@ -210,7 +211,8 @@ size_t vs_noalloc_scratch_bytes(void);
  * 2 / (M (12/h^2) [C_b (2 + 12 eps^2/h^2)^2 + 12 |gamma_A|/h^2]) (bending) or
  * 2 / (M (12/h^2)(2 + 12 sigma/h^2)) (Cahn–Hilliard), unless VS_ALLOW_UNSTABLE is set.
  * Device-side failures (VS_E_NOCONV, VS_E_NONFINITE) are reported at the end of the call,
- * after all nsteps have run. Synchronises the stream once, at the end. With rho > 0 the
+ * after all nsteps have run. Synchronises the stream at the end and, in VS_FP64 with
+ * poisson_max_cycles > 1, once more where a step missed poisson_rtol. With rho > 0 the
  * first call with a new dt also synchronises before it enqueues anything, to upload that
  * dt's vorticity pivots (so it cannot run under stream capture). */
 vs_status vs_step(vs_state* state, double dt, int32_t nsteps);
@@ -229,7 +231,9 @@ vs_status vs_step(vs_state* state, double dt, int32_t nsteps);
  * adj_next, adj_prev: device, nx*ny*nz doubles each, z fastest, must not alias; dparams: host,
  * 2 doubles, accumulated. The two adjoint Poisson solves are verified to poisson_rtol like the
  * forward ones (VS_E_NOCONV otherwise). The state's fields are left unchanged (the reverse
- * step uses the spectral scratch and the spare phi buffer). Synchronises the stream once. */
+ * step uses the spectral scratch and the spare phi buffer). Synchronises the stream once for
+ * each form that runs: both adjoint solves in one pass, or each with correction cycles after that
+ * missed poisson_rtol (poisson_max_cycles > 1). */
 vs_status vs_grad_step(vs_state* state, double dt, const double* adj_next, double* adj_prev,
                        double dparams[2]);
 
@@ -300,13 +304,14 @@ vs_status vs_profile_read(vs_state* state, int32_t kernel, double* total_ms, int
 /* Launch-shape autotuner. A grid starts with launch shapes that a rule on its sizes picks.
  * vs_autotune times, on the state's own data, the candidate launch shapes of its grid: the x-slab
  * length of the phi update (2, 4, 8 planes per lane), the block caps of the
- * volume/area partials (256 .. 2048) and of the flow residual (512 .. 4096), the form of the
- * chemical potential (LDS tiles, or for nz <= 128, or nz <= 256 and a multiple of 4, register
- * marching with 1 or 2 rows per lane group and 2 .. 16 planes per slab; all forms give the same
- * bits) and, for
- * ny - 2 in {30, 46, 62, 94, 126, 254}, the segment layout of the tridiagonal solves (the
+ * volume/area partials (256 .. 2048) and of the flow residual (512 .. 4096), for nz <= 128, or
+ * nz <= 256 and a multiple of 4, the rows per lane group (1 or 2) and planes per slab (2 .. 16) of
+ * the register-marching chemical potential (other grids run it on LDS tiles; all forms give the
+ * same bits), for
+ * ny - 2 in {30, 46, 62, 94, 126, 254} the segment layout of the tridiagonal solves (the
  * default or one with twice/half the lanes per mode) and, in FP64 with nx and nz in
- * {32, 48, 64, 96, 128}, whether the x and z transforms of a direction run as one pass over
+ * {32, 48, 64, 96, 128}, or both in {16, 24, 32, 36, 48, 54, 64, 72, 96, 108} with a plane of at
+ * most 79 KB in LDS, whether the x and z transforms of a direction run as one pass over
  * each (x, z) plane held in LDS (plane = 1) or as two line passes (0), one coordinate at a
  * time, and keeps the fastest for every state of that grid in this process. The state's fields
  * are not changed. picked (may be NULL): adv_slab, va_maxb, res_maxb, seg_alt, mu_kind, mu_ni,
@@ -335,7 +340,10 @@ vs_status vs_set_launch_shapes(const vs_grid* grid, const int32_t shapes[7]);
  * g % nstreams) and moves every state onto its stream; `stream` (a hipStream_t, NULL =
  * default) is the origin the batch forks from and joins to. vs_batch_step captures two time
  * steps of every class into one HIP graph (redone when a dt or a wall speed changes) and
- * replays it nsteps/2 times on the origin stream. nsteps must be even. dt: host array of n
+ * replays it nsteps/2 times on the origin stream. An instance with poisson_max_cycles > 1 in VS_FP64
+ * whose step misses poisson_rtol stops there and is finished after the replays; where every
+ * instance's last call corrected most of its steps, the steps are enqueued without the graph.
+ * nsteps must be even. dt: host array of n
  * time steps. Each instance is checked against its stability bound first; statuses are
  * collected after one synchronisation (the first failing instance's status is returned).
  * Results are bitwise those of stepping each instance alone. vs_batch_destroy frees the batch

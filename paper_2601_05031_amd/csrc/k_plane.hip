@@ -12,7 +12,7 @@ namespace {
 
 // ---------------------------------------------------------------------------------------
 // Both transform directions of one interior row in one pass: the whole (x, z) plane of row j
-// and one component sits in LDS (n_x (n_z + 2) doubles, 133 KB at 128 x 128), so the spectral
+// and one component sits in LDS (n_x rows of plane_row doubles, 132 KB at 128 x 128), so the spectral
 // data crosses HBM once per direction instead of twice. Each 1D
 // transform is the two-pass form above done in place in the plane: pass 1 overwrites the B
 // inputs of its (line pair, k1), or with the swizzle below those of its line pair, with their twiddled
@@ -272,8 +272,8 @@ __global__ __launch_bounds__((PlaneShape<BX, AX, BZ, AZ>::NT), (PlaneShape<BX, A
 }
 
 // The refined mode's plane passes: FP32 spectral data, the (x, z) plane of one interior row
-// and component in LDS as floats (n_x (n_z + 2) floats: 66 KB at 128 x 128). ZFIRST: the forward transforms, z then x, of the FP32 residuals in place
-// (z.spec[c], c < 6: vorticity then stream vector). Otherwise the inverse transforms, x then z,
+// and component in LDS as floats (n_x rows of plane_row floats: 66 KB at 128 x 128). ZFIRST: the forward
+// transforms, z then x, of the FP32 residuals in place (z.spec[c], c < 6: vorticity then stream vector). Otherwise the inverse transforms, x then z,
 // of the FP32 corrections (x.spec[c]) added to the FP64 fields (z.u[c]) as k_hz_out adds them:
 // the time increments of the first cycle's update (z.inc, z.pinc, z.hist, z.hist_out) or of a
 // later cycle (z.inc), or a plain add (z.add, the initial solve). Planes of an instance whose

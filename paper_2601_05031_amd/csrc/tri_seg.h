@@ -257,8 +257,9 @@ __device__ __forceinline__ void seg_store(const ST (&x)[LMAX], ST* base, unsigne
 // segment lengths and long-segment counts as compile-time constants, other M in [17, 256] in FP64
 // the length alone: with a run-time length every row of the unrolled loops sits behind a branch,
 // which keeps the loads from being in flight together (pair solves at
-// 72 x 51 x 108 17.9 -> 9.2 us, 96 x 112 x 96 32 -> 17, 128 x 120 x 128 66 -> 26). M below 17, and FP32,
-// take a run-time length.
+// 72 x 51 x 108 17.9 -> 9.2 us, 96 x 112 x 96 32 -> 17, 128 x 120 x 128 66 -> 26). M below 17 and FP32
+// with another M than those of the six grids take a run-time length (compile-time ones were not
+// measured there).
 #define VS_SEG_L(X, C, S_, L_) case C + L_: X(S_, L_, L_, -1); return true;
 #define VS_SEG_L8(X, C, S_)                                                                    \
     VS_SEG_L(X, C, S_, 9) VS_SEG_L(X, C, S_, 10) VS_SEG_L(X, C, S_, 11) VS_SEG_L(X, C, S_, 12) \

@@ -494,7 +494,9 @@ struct StepArgs {
 // hand-off between kernels stays in the 256 MB Infinity Cache, which pays where 18 fields do
 // not fit and 12 at least half do (per step: 128^3 248 -> 230 us, 128 x 128 x 256 477 -> 453 us,
 // eight instances of 4.7 M nodes 561 -> 541 us). Where all 18 fit, or neither, rewriting the
-// lines just read costs a little (64^3 73 -> 78 us, 256^3 2326 -> 2345 us).
+// lines just read costs a little (64^3 73 -> 78 us, 256^3 2326 -> 2345 us). No point between 4.7 and
+// 16.8 M nodes stands behind the upper bound (12 fields in twice the cache: 5.6 M nodes); a batch of
+// three 128^3 states (6.3 M) lies above it.
 bool modes_in_place(double nodes) {
     constexpr double kCache = 256.0 * 1024.0 * 1024.0;
     return 18.0 * 8.0 * nodes > kCache && 12.0 * 8.0 * nodes <= 2.0 * kCache;
